@@ -11,44 +11,9 @@
 // padding of the packed weights (finite x 0 adds nothing).  Epilogues load the bias before any
 // store and read the problem fields into scalar registers once: a load between the stores
 // would make every store wait for all earlier ones (the memory counter counts both).
-#include "mt_internal.h"
+#include "mt_gemm_common.h"
 
 namespace mt {
-
-template <typename T>
-__device__ __forceinline__ T pin_s(T x) {  // keep a uniform value in a scalar register
-  asm volatile("" : "+s"(x));
-  return x;
-}
-
-struct Problems {
-  GemmProblem p[2];
-};
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
-template <typename T>
-__device__ __forceinline__ T bitcast16(const u32x4 &v) {
-  T r;
-  __builtin_memcpy(&r, &v, 16);
-  return r;
-}
-
-__device__ __forceinline__ u32x4 pack_bf16x8(const u32x4 &lo, const u32x4 &hi) {
-  float a[4], b[4];
-  __builtin_memcpy(a, &lo, 16);
-  __builtin_memcpy(b, &hi, 16);
-  bf16x8 h;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    h[j] = to_bf16(a[j]);
-    h[4 + j] = to_bf16(b[j]);
-  }
-  u32x4 r;
-  __builtin_memcpy(&r, &h, 16);
-  return r;
-}
 
 // ---------------------------------------------------------------------------------------
 // bf16 operands: weights streamed from global memory straight into registers.
@@ -644,6 +609,26 @@ static hipError_t go_f32(const Problems &ps, int nprob, hipStream_t st) {
   }
 }
 
+// Few rows take the split-depth kernel of mt_gemm_small.hip, counted in its workgroups (32 rows x
+// one column block).  Where the lines lie (us, tiles above against small; 5120 x 1024 s1 product,
+// 3584 x 2048 context product, 3072 x 1024 recurrent product):
+//  * bf16, 512 workgroups: s1 at 96 rows (480) 8.3 / 6.0 and 128 (640) 8.4 / 7.7, context at 128
+//    (448) 12.0 / 8.4 and 256 (896) 12.4 / 13.1, recurrent at 128 (384) 8.6 / 6.5, two recurrent
+//    products at 64 rows (384) 8.5 / 6.9 and at 96 (576) 8.7 / 9.0;
+//  * fp32 in the 32-column packing, whose tiles are the coarser ones, 896: context at 5 rows 38.5
+//    / 7.9, at 128 (896) 39.6 / 29.1, at 256 40.0 / 45.9;
+//  * fp32 in the 16-column packing, 256: recurrent at 32 rows (192) 7.1 / 6.7, readout at 256
+//    (256) 6.8 / 6.2, but s1 at 5 rows (320) 6.7 / 8.1 and two recurrent products at 5 (384) 7.2 / 8.2.
+static bool small_rows(int bf16_mma, const Problems &ps, int nprob) {
+  long wg = 0;
+  for (int i = 0; i < nprob; ++i) {
+    const GemmProblem &p = ps.p[i];
+    if (p.K % 16 != 0 || p.M < 1 || p.wblk != ps.p[0].wblk) return false;
+    wg += (long)((p.M + 31) / 32) * ((p.N + (bf16_mma ? 31 : 15)) / (bf16_mma ? 32 : 16));
+  }
+  return wg <= (bf16_mma ? 512 : ps.p[0].wblk == 32 ? 896 : 256);
+}
+
 hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilogue epi, hipStream_t st) {
   Problems ps{};
   for (int i = 0; i < nprob; ++i) {
@@ -651,6 +636,7 @@ hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilog
     if (probs[i].a_bf16 != probs[0].a_bf16 || (probs[i].a_bf16 && !bf16_mma)) return hipErrorInvalidValue;
     if (epi == EPI_SCATTER && !probs[i].a_idx) return hipErrorInvalidValue;
   }
+  if (small_rows(bf16_mma, ps, nprob)) return launch_gemm_small(bf16_mma, ps, nprob, epi, st);
   if (!bf16_mma) {
     if (epi == EPI_SCATTER) return go_f32<EPI_SCATTER>(ps, nprob, st);
     return epi == EPI_TANH ? go_f32<EPI_TANH>(ps, nprob, st) : go_f32<EPI_STORE>(ps, nprob, st);
