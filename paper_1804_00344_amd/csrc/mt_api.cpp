@@ -41,6 +41,7 @@ constexpr int kKPadFrag = 128;            // K padding of bf16 weights (one LDS 
 // (64 sentences x beam 12, their 5000 or so source positions, the sentences): a model serves
 // any batch, only the speed of other row counts may differ.
 constexpr long kRefRows = 768, kRefCtxRows = 4096, kRefSentences = 64;
+constexpr int kEncFusedSentences = 256;  // see mt_encode
 constexpr int kMaxTransitions = 16;  // recurrent-only GRU blocks after GRU 2
 
 size_t rup(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -647,9 +648,10 @@ size_t mt_workspace_bytes(const mt_model *m, int B, int K, int S) {
 
 // encoder workspace: input products [B*S][6H], recurrent products of both directions and a
 // zero block [B][3H] each, fp32 states [2 directions][2][B][H] (bf16 models), intermediate
-// states of the transition blocks [2 directions][B][H]
+// states of the transition blocks [2 directions][B][H] and their bf16 copies, the lists of launch_enc_lists (valid
+// entries and their tokens [B*S] each, rows per position [S][B], the two counts [1 + S])
 struct EncLayout {
-  size_t xe, uf, ub, uz, st, tx, total;
+  size_t xe, uf, ub, uz, st, tx, tx16, vrow, vtok, act, cnt, total;
 };
 static EncLayout enc_layout(const mt_model *m, int B, int S) {
   const size_t H = m->cfg.H;
@@ -666,6 +668,11 @@ static EncLayout enc_layout(const mt_model *m, int B, int S) {
   L.uz = take((size_t)B * 3 * H * 4);
   L.st = take(m->bf16 ? (size_t)4 * B * H * 4 : 0);
   L.tx = take(m->cfg.enc_transitions > 0 ? (size_t)2 * B * H * 4 : 0);
+  L.tx16 = take(m->cfg.enc_transitions > 0 && m->bf16 ? (size_t)2 * B * H * 2 : 0);
+  L.vrow = take((size_t)B * S * 4);
+  L.vtok = take((size_t)B * S * 4);
+  L.act = take((size_t)B * S * 4);
+  L.cnt = take((size_t)(S + 1) * 4);
   L.total = off;
   return L;
 }
@@ -695,19 +702,46 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
   float *xe = (float *)(W + L.xe), *uf = (float *)(W + L.uf), *ub = (float *)(W + L.ub), *uz = (float *)(W + L.uz);
   float *sst = (float *)(W + L.st);  // bf16 models: [dir][parity][B][H]
   const long ldc = (long)S * C;      // row stride of one sentence's positions in ctx_out
-  // input side of every position and both directions: semb[src_tok] [Wef | Web] + [bef | beb]
+  // the valid positions and the rows valid at each of them: a padded position carries the state
+  // over, so the input products are computed at the valid ones and a recurrent product runs
+  // over the rows of its position
+  int32_t *vrow = (int32_t *)(W + L.vrow), *vtok = (int32_t *)(W + L.vtok), *act = (int32_t *)(W + L.act);
+  int *nvalid = (int *)(W + L.cnt), *acnt = nvalid + 1;
+  LAUNCH(MT_KERNEL_ENCODE, launch_enc_lists(B, S, mask, src_tok, model->cfg.src_V, vrow, vtok, nvalid, act, acnt,
+                                            model->err, st));
+  // input side of both directions: semb[src_tok] [Wef | Web] + [bef | beb]
   GemmProblem px{};
-  px.A = model->semb; px.a_idx = src_tok; px.a_rows = model->cfg.src_V; px.lda = E; px.a_bf16 = 0;
+  px.A = model->semb; px.a_idx = vtok; px.a_rows = model->cfg.src_V; px.lda = E; px.a_bf16 = 0;
   px.Bp = model->wenc_x.p; px.ldb = model->wenc_x.ldb; px.wblk = model->wenc_x.blk; px.bias = model->bias_enc;
   px.out = xe; px.ldc = 6 * H; px.M = B * S; px.N = 6 * H; px.K = E; px.err = model->err; px.err_bit = 3;
-  LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, &px, 1, EPI_STORE, st));
-  LAUNCH(MT_KERNEL_ENCODE, launch_fill_zero(uz, (long long)B * 3 * H, st));
+  px.o_idx = vrow; px.m_dev = nvalid;
+  LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, &px, 1, EPI_SCATTER, st));
   float *c32 = bf ? nullptr : (float *)ctx_out;
   bf16 *c16 = bf ? (bf16 *)ctx_out : nullptr;
   const int Te = model->cfg.enc_transitions;
   float *tx = (float *)(W + L.tx);  // intermediate transition states [dir][B][H]
+  bf16 *tx16 = (bf16 *)(W + L.tx16);  // bf16 models: the operand of the next block's product
   float *const *eln = model->cfg.enc_layer_norm ? model->ln_enc : nullptr;
   const float eps = model->cfg.ln_eps;
+  // A shallow cell up to 256 sentences: one kernel per position.  Above, its 32-row groups read
+  // the weights too often (40 positions, two launches against one: bf16 128 sentences 675 / 487 us,
+  // 256 956 / 880, 1000 2645 / 3144; fp32 1586 / 1285, 2632 / 2499, 8930 / 9654).
+  if (Te == 0 && !eln && B <= kEncFusedSentences) {
+    if (bf) LAUNCH(MT_KERNEL_ENCODE, launch_fill_zero(sst, (long long)2 * B * H, st));
+    EncStep e{};
+    e.B = B; e.S = S; e.H = H;
+    e.w[0] = model->wenc_f.p; e.w[1] = model->wenc_b.p;
+    e.ldb = model->wenc_f.ldb; e.wblk = model->wenc_f.blk;
+    e.xe = xe; e.ctx = ctx_out; e.ldc = ldc; e.sst = sst; e.mask = mask; e.act = act; e.acnt = acnt;
+    for (int n = 0; n < S; ++n) {
+      e.first = n == 0;
+      e.pos[0] = n; e.pos[1] = S - 1 - n;
+      e.prv[0] = n - 1; e.prv[1] = S - n;
+      LAUNCH(MT_KERNEL_ENCODE, launch_enc_step(bf, e, st));
+    }
+    return MT_OK;
+  }
+  LAUNCH(MT_KERNEL_ENCODE, launch_fill_zero(uz, (long long)B * 3 * H, st));
   for (int n = 0; n < S; ++n) {
     const int pos[2] = {n, S - 1 - n};       // forward, backward position of this pass
     const int prv[2] = {n - 1, S - n};       // the position each direction comes from
@@ -733,8 +767,9 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
         const Packed &U = d == 0 ? model->wenc_f : model->wenc_b;
         pr[d].Bp = U.p; pr[d].ldb = U.ldb; pr[d].wblk = U.blk;
         pr[d].out = d == 0 ? uf : ub; pr[d].ldc = 3 * H; pr[d].M = B; pr[d].N = 3 * H; pr[d].K = H;
+        pr[d].a_idx = act + (size_t)pos[d] * B; pr[d].m_dev = acnt + pos[d];
       }
-      LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, pr, 2, EPI_STORE, st));
+      LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, pr, 2, EPI_SCATTER, st));
     }
     // one launch runs both directions' cells (the second at element offsets from the first)
     struct CellArgs {
@@ -763,14 +798,14 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
           ldh = (int)ldc;
         }
         ca[d] = {xe + (size_t)pos[d] * 6 * H + (size_t)d * 3 * H, n > 0 ? (d == 0 ? uf : ub) : uz, hsrc,
-                 block_out(d, 0).p, bf && Te == 0 ? c16 + oc : nullptr, mask + pos[d]};
+                 block_out(d, 0).p, !bf ? nullptr : Te == 0 ? c16 + oc : tx16 + (size_t)d * B * H, mask + pos[d]};
       }
       const CellPair pr = pair_of(ca[0], ca[1], 3 * H);
       LAUNCH(MT_KERNEL_ENCODE,
              launch_gru_cell_ex(B, H, ca[0].a, S * 6 * H, nullptr, B, ca[0].u, 3 * H, ca[0].h, ldh, nullptr, B,
                                 model->err, eln ? eln[0] : nullptr, eln ? eln[1] : nullptr, eln ? eln[2] : nullptr,
-                                eln ? eln[3] : nullptr, eps, ca[0].out, block_out(0, 0).ld, ca[0].o16, (int)ldc,
-                                nullptr, ca[0].keep, S, st, &pr));
+                                eln ? eln[3] : nullptr, eps, ca[0].out, block_out(0, 0).ld, ca[0].o16,
+                                Te == 0 ? (int)ldc : H, nullptr, ca[0].keep, S, st, &pr));
     }
     // transition blocks: recurrent products of both directions, then both directions' cells
     // with the bias as the whole input path (lda = 0); a padded position keeps its state
@@ -778,17 +813,19 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
       GemmProblem pt[2]{};
       for (int d = 0; d < 2; ++d) {
         const Slot x = block_out(d, j);
-        pt[d].A = x.p; pt[d].a_rows = B; pt[d].lda = x.ld; pt[d].a_bf16 = 0;
+        pt[d].A = bf ? (const void *)(tx16 + (size_t)d * B * H) : x.p;
+        pt[d].a_rows = B; pt[d].lda = bf ? H : x.ld; pt[d].a_bf16 = bf;
         const Packed &U = d == 0 ? model->wenc_tf[j] : model->wenc_tb[j];
         pt[d].Bp = U.p; pt[d].ldb = U.ldb; pt[d].wblk = U.blk;
         pt[d].out = d == 0 ? uf : ub; pt[d].ldc = 3 * H; pt[d].M = B; pt[d].N = 3 * H; pt[d].K = H;
+        pt[d].a_idx = act + (size_t)pos[d] * B; pt[d].m_dev = acnt + pos[d];
       }
-      LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, pt, 2, EPI_STORE, st));
+      LAUNCH(MT_KERNEL_ENCODE, launch_gemm(bf, pt, 2, EPI_SCATTER, st));
       CellArgs ca[2];
       for (int d = 0; d < 2; ++d) {
         const size_t oc = (size_t)pos[d] * C + (size_t)d * H;
         ca[d] = {model->bias_tenc + (size_t)(2 * j + d) * 3 * H, d == 0 ? uf : ub, block_out(d, j).p,
-                 block_out(d, j + 1).p, bf && j + 1 == Te ? c16 + oc : nullptr, mask + pos[d]};
+                 block_out(d, j + 1).p, !bf ? nullptr : j + 1 == Te ? c16 + oc : tx16 + (size_t)d * B * H, mask + pos[d]};
       }
       const CellPair pr = pair_of(ca[0], ca[1], (long long)Te * 3 * H);
       const size_t to = (size_t)j * 3 * H;  // forward direction's block j
@@ -796,7 +833,7 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
              launch_gru_cell_ex(B, H, ca[0].a, 0, nullptr, B, ca[0].u, 3 * H, ca[0].h, block_out(0, j).ld, nullptr,
                                 B, model->err, nullptr, nullptr, eln ? eln[4] + to : nullptr,
                                 eln ? eln[5] + to : nullptr, eps, ca[0].out, block_out(0, j + 1).ld, ca[0].o16,
-                                (int)ldc, nullptr, ca[0].keep, S, st, &pr));
+                                j + 1 == Te ? (int)ldc : H, nullptr, ca[0].keep, S, st, &pr));
     }
   }
   return MT_OK;

@@ -196,8 +196,8 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   // EPI_SCATTER: the output row of each stored row is its (clamped) gather row
   int orow[EPI == EPI_SCATTER ? MB : 1][16];
   if constexpr (EPI == EPI_SCATTER) {
-    const int32_t *const aix = pin_s(P.a_idx);
-    const int arows = pin_s(P.a_rows);
+    const int32_t *const aix = pin_s(P.o_idx ? P.o_idx : P.a_idx);
+    const int arows = pin_s(P.o_idx ? 0x7fffffff : P.a_rows);
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
@@ -454,8 +454,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
   // EPI_SCATTER: the output row of each stored row is its (clamped) gather row
   int orow[EPI == EPI_SCATTER ? TA : 1][EPI == EPI_SCATTER ? F::NACC : 1];
   if constexpr (EPI == EPI_SCATTER) {
-    const int32_t *const aix = pin_s(P.a_idx);
-    const int arows = pin_s(P.a_rows);
+    const int32_t *const aix = pin_s(P.o_idx ? P.o_idx : P.a_idx);
+    const int arows = pin_s(P.o_idx ? 0x7fffffff : P.a_rows);
 #pragma unroll
     for (int i = 0; i < TA; ++i)
 #pragma unroll
@@ -641,8 +641,8 @@ hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilog
     if (epi == EPI_SCATTER) return go_f32<EPI_SCATTER>(ps, nprob, st);
     return epi == EPI_TANH ? go_f32<EPI_TANH>(ps, nprob, st) : go_f32<EPI_STORE>(ps, nprob, st);
   }
-  if (epi == EPI_SCATTER)  // the keys precompute: bf16 context rows
-    return probs[0].a_bf16 ? go_wd<bf16, EPI_SCATTER>(ps, nprob, st) : hipErrorInvalidValue;
+  if (epi == EPI_SCATTER)
+    return probs[0].a_bf16 ? go_wd<bf16, EPI_SCATTER>(ps, nprob, st) : go_wd<float, EPI_SCATTER>(ps, nprob, st);
   if (probs[0].a_bf16)
     return epi == EPI_TANH ? go_wd<bf16, EPI_TANH>(ps, nprob, st) : go_wd<bf16, EPI_STORE>(ps, nprob, st);
   return epi == EPI_TANH ? go_wd<float, EPI_TANH>(ps, nprob, st) : go_wd<float, EPI_STORE>(ps, nprob, st);

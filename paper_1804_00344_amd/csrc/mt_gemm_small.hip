@@ -47,18 +47,11 @@ __global__ __launch_bounds__(kSmThreads, 4) void gemm_small_kernel(Problems prob
   const int rg = id % rgs, nb = id / rgs;  // neighbours share a column block
   if (nb >= (N + BLK - 1) / BLK) return;
   const int m0 = rg * kSmRows;
-  // rows counted on the device, when given, bound the rows read and stored
-  const int *const mdp = pin_s(P.m_dev);
-  int Mv = M;
-  if (mdp) {
-    const int md = *(const __attribute__((address_space(1))) int *)mdp;
-    Mv = md < M ? md : M;
-  }
-  if (m0 >= Mv) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- this wave's k-steps; the first chunk's weights are requested before the row indices ----
+  // ---- this wave's k-steps; the first chunk's weights and the row indices are requested before
+  // the row count is waited for ----
   const int s_begin = KS * wave / kSmWaves, s_end = KS * (wave + 1) / kSmWaves;
   const int n = s_end - s_begin;
   typedef u32x4 BSet[F::STEPS];
@@ -75,7 +68,18 @@ __global__ __launch_bounds__(kSmThreads, 4) void gemm_small_kernel(Problems prob
       b[d] = *(const u32x4 *)(wp + (size_t)(s < s_end ? s : KS - 1) * WSTEP);  // past the end: never used
     }
   };
+  const int mrow = m0 + (lane & (kSmRows - 1));
+  int myrow = mrow;
+  if (P.a_idx) myrow = P.a_idx[mrow < M ? mrow : M - 1];
   load_b(0, b0);
+  // rows counted on the device, when given, bound the rows read and stored
+  const int *const mdp = pin_s(P.m_dev);
+  int Mv = M;
+  if (mdp) {
+    const int md = *(const __attribute__((address_space(1))) int *)mdp;
+    Mv = md < M ? md : M;
+  }
+  if (m0 >= Mv) return;
 
   // ---- activations: 64-k row pieces into this wave's LDS (16-byte vectors, one row's vectors
   // in consecutive lanes: a load instruction touches the full cache lines of four or eight rows.
@@ -84,18 +88,14 @@ __global__ __launch_bounds__(kSmThreads, 4) void gemm_small_kernel(Problems prob
   constexpr int VR = F::KC * (int)sizeof(AT) / 16;  // vectors per row piece
   constexpr int RPI = 64 / VR;      // rows per load instruction
   constexpr int NI = kSmRows / RPI;
-  int myrow;
-  {
-    const int m = m0 + (lane & (kSmRows - 1));
-    myrow = m < Mv ? m : 0;
-    if (P.a_idx && m < Mv) {
-      myrow = P.a_idx[m];
-      if (myrow < 0 || myrow >= P.a_rows) {
-        if (P.err) atomicOr(P.err, 1 << P.err_bit);
-        myrow = myrow < 0 ? 0 : P.a_rows - 1;
-      }
-    }
+  if (mrow >= Mv) {
+    myrow = 0;
+  } else if (P.a_idx && (myrow < 0 || myrow >= P.a_rows)) {
+    if (P.err) atomicOr(P.err, 1 << P.err_bit);
+    myrow = myrow < 0 ? 0 : P.a_rows - 1;
   }
+  int myout = myrow;  // EPI_SCATTER: the (clamped) gather row, or o_idx
+  if (EPI == EPI_SCATTER && P.o_idx) myout = P.o_idx[mrow < Mv ? mrow : m0];
   const int vec = lane % VR;
   const char *ap[NI];
 #pragma unroll
@@ -185,11 +185,21 @@ __global__ __launch_bounds__(kSmThreads, 4) void gemm_small_kernel(Problems prob
 
   // ---- the waves' partial tiles, added in wave order ----
   float *const red = (float *)lds;
+  auto row_of = [&](int e) {
+    const int l = e & 63, r = (e >> 6) % F::NACC, i = (e >> 6) / F::NACC;
+    return m0 + BLK * i + (BLK == 16 ? (l >> 4) * 4 + r : 8 * (r >> 2) + 4 * (l >> 5) + (r & 3));
+  };
 #pragma unroll
   for (int i = 0; i < F::RB; ++i)
 #pragma unroll
     for (int r = 0; r < F::NACC; ++r) red[wave * PER + (i * F::NACC + r) * 64 + lane] = acc[i][r];
   __syncthreads();
+  // EPI_SCATTER: the output row of each element (lane l of every wave holds that of row m0 + l % 32)
+  int orow[EPI == EPI_SCATTER ? PER / kSmThreads : 1];
+  if constexpr (EPI == EPI_SCATTER) {
+#pragma unroll
+    for (int q = 0; q < PER / kSmThreads; ++q) orow[q] = __shfl(myout, row_of(tid + kSmThreads * q) - m0, 64);
+  }
   const int obf = pin_s(P.out_bf16);
   const float *const biasp = pin_s(P.bias);
   char *const outp = (char *)pin_s(P.out);
@@ -200,17 +210,12 @@ __global__ __launch_bounds__(kSmThreads, 4) void gemm_small_kernel(Problems prob
 #pragma unroll
     for (int w = 1; w < kSmWaves; ++w) v += red[w * PER + e];
     // element e = (row block, accumulator r, lane l) of the MFMA output layout
-    const int l = e & 63, r = (e >> 6) % F::NACC, i = (e >> 6) / F::NACC;
-    const int row = m0 + BLK * i + (BLK == 16 ? (l >> 4) * 4 + r : 8 * (r >> 2) + 4 * (l >> 5) + (r & 3));
-    const int col = nb * BLK + (l & (BLK - 1));
+    const int row = row_of(e);
+    const int col = nb * BLK + (e & (BLK - 1));
     if (row >= Mv || col >= N) continue;
     if (biasp) v += biasp[col];
     if (EPI == EPI_TANH) v = tanh_fast(v);
-    int orw = row;
-    if constexpr (EPI == EPI_SCATTER) {
-      const int g = P.a_idx[row], ar = P.a_rows;
-      orw = g < 0 ? 0 : g >= ar ? ar - 1 : g;
-    }
+    const int orw = EPI == EPI_SCATTER ? orow[q] : row;
     if (obf)
       ((bf16 *)outp)[(size_t)orw * ldc + col] = to_bf16(v);
     else

@@ -568,7 +568,7 @@ __device__ __forceinline__ void row_recompute_ens(const VocabView *vvs, const fl
 // launchers (host side).  All return hipSuccess or the launch error.
 // ---------------------------------------------------------------------------------------
 
-// EPI_SCATTER: row m is stored at output row a_idx[m] (the rows it was gathered from)
+// EPI_SCATTER: row m is stored at output row o_idx[m], or a_idx[m] (the rows it was gathered from)
 enum Epilogue { EPI_STORE = 0, EPI_TANH = 1, EPI_SCATTER = 2 };
 
 struct GemmProblem {
@@ -587,6 +587,7 @@ struct GemmProblem {
   int32_t *err;           // device error word (bit err_bit set on a clamped gather)
   int err_bit;
   int wblk;               // fp32 weights: column block width of their packing (16 or 32)
+  const int32_t *o_idx;   // EPI_SCATTER: output row of each row (NULL: a_idx); in range
   const int *m_dev;       // optional: row count on the device (<= M); later rows are neither
                           // read nor stored, and tiles that start past it return at once
 };
@@ -697,6 +698,27 @@ hipError_t launch_gru_cell_ex(int M, int H, const float *a, int lda, const int32
                               int32_t *err, const float *ga, const float *ba, const float *gu, const float *bu,
                               float eps, float *out, int ldo, bf16 *out16, int ld16, float *tap,
                               const float *keep, int keep_ld, hipStream_t st, const CellPair *pair = nullptr);
+// ---- encoder recurrence (mt_encoder.hip) ----
+// vrow/vtok [B*S]: the valid entries of mask [B][S] in order and their tokens, *nvalid of them;
+// act [S][B], acnt [S]: the sentences valid at each position; tokens out of range set bit 3 of err
+hipError_t launch_enc_lists(int B, int S, const float *mask, const int32_t *tok, int src_V, int32_t *vrow,
+                            int32_t *vtok, int *nvalid, int32_t *act, int *acnt, int32_t *err, hipStream_t st);
+// One position of both directions of a shallow encoder cell (no layer norm, no transition
+// blocks): direction d moves from position prv[d] to pos[d]; first: zero previous state.
+struct EncStep {
+  int B, S, H, first;
+  int pos[2], prv[2];
+  const void *w[2];    // packed recurrent weights of each direction
+  int ldb, wblk;       // their K_pad and (fp32) column block width
+  const float *xe;     // [B*S][6H] input gates, forward then backward (valid positions)
+  void *ctx;           // [B][S][2H] states in the GEMM type, ldc elements per sentence
+  long long ldc;
+  float *sst;          // bf16 models: fp32 states [direction][B][H], updated in place
+  const float *mask;
+  const int32_t *act;  // launch_enc_lists
+  const int *acnt;
+};
+hipError_t launch_enc_step(int bf16_mma, const EncStep &p, hipStream_t st);
 hipError_t launch_fill_zero(float *p, long long n, hipStream_t st);
 
 hipError_t launch_readout(int M, int E, const float *p1, int ld1, const float *p2, int ld2, const int32_t *idx2,

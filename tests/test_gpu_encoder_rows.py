@@ -1,0 +1,65 @@
+"""The encoder's recurrence over the rows valid at each position: masks with holes, sentences
+without a valid position, row counts around the 32-row groups and the 16-row blocks, depths that
+are no multiple of a k-step, against the oracle's encoder at every position."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import mtref
+from paper_1804_00344_amd import synth
+from parity_util import TOL, maxerr
+
+if torch.cuda.is_available():
+    from paper_1804_00344_amd import mtstep as mt
+    from paper_1804_00344_amd.runner import Decoder
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def encoder(gemm, E, H, src_V, T, ln):
+    p = synth.with_sizes(synth.PRESETS["tiny_bf16_ln" if gemm == "bf16" else "tiny_f32"], E=E, H=H, A=32)
+    w = synth.make_weights(p)
+    ew = synth.make_encoder_weights(p, src_V, transitions=T, layer_norm=ln)
+    dec = Decoder(p.E, p.H, p.A, p.V, {**w, **ew}, gemm=gemm, layer_norm=p.layer_norm, k_max=4, src_V=src_V,
+                  enc_transitions=T, enc_layer_norm=ln)
+    return p, ew, dec
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H,T,ln", [(1, 64, 0, False), (16, 80, 0, False), (17, 208, 0, False), (33, 64, 0, False),
+                                      (65, 1024, 0, False), (33, 80, 1, True), (65, 64, 0, True)])
+def test_encoder_masks_with_holes(B, H, T, ln, gemm):
+    S, src_V = 6, 60
+    p, ew, dec = encoder(gemm, 48, H, src_V, T, ln)
+    rng = np.random.default_rng(B + H)
+    mask = (rng.random((B, S)) < 0.6).astype(np.float32)
+    mask[:, S - 2] = 1.0       # a position with every row,
+    mask[:, 2] = 0.0           # one with none
+    mask[0, 1:] = 0.0
+    mask[0, 0] = 1.0
+    if B > 1:
+        mask[B - 1] = 0.0      # a sentence without a valid position
+    src = rng.integers(0, src_V, size=(B, S)).astype(np.int32)
+    dec.set_source(src, mask, 1)
+    got = dec.ctx.float().cpu().numpy()
+    assert mt.mt_device_errors(dec.model) == 0
+    trans = tuple(ew[k] for k in synth.ENCODER_TRANSITION_NAMES) if T else None
+    lnp = tuple(ew[k] for k in synth.ENCODER_LN_NAMES if k in ew) if ln else None
+    ref = mtref.encode(src, mask, *[ew[k] for k in synth.ENCODER_NAMES], transitions=trans, ln=lnp, eps=1e-5)
+    err = maxerr(got, ref)
+    print(f"encoder {gemm} B={B} H={H} T={T} ln={ln}: max error {err:.3g}", flush=True)
+    assert err <= TOL[gemm]["state"]
+
+
+def test_encoder_flags_padded_tokens_out_of_range():
+    p, ew, dec = encoder("f32", 48, 64, 50, 0, False)
+    mask = np.array([[1, 1, 0]], np.float32)
+    dec.set_source(np.array([[3, 4, 50]], np.int32), mask, 1)  # at padding: flagged, not read
+    assert mt.mt_device_errors(dec.model) == 8
+    good = dec.ctx.cpu().numpy()
+    dec.set_source(np.array([[3, 4, 0]], np.int32), mask, 1)
+    assert mt.mt_device_errors(dec.model) == 0
+    assert np.array_equal(good, dec.ctx.cpu().numpy())
+    dec.set_source(np.array([[3, -1, 0]], np.int32), mask, 1)
+    assert mt.mt_device_errors(dec.model) == 8
