@@ -1004,12 +1004,14 @@ static mt_status decoder_step_impl(mt_model *model, int B, int K, int S, const i
   // model (any permutation of the B sentences gives the same results: it only schedules)
   const int *srank1 = model->srank_B[0] == B ? model->srank[0] : nullptr;
   const int *srank2 = model->srank_B[1] == B ? model->srank[1] : nullptr;
+  // the scores of the beam form lie where the context products will (rows of 3H + E floats)
+  auto scores = [&](int s) { return s <= 3 * H + E ? g3 : nullptr; };
   LAUNCH(MT_KERNEL_ATTENTION, launch_attention(B, K, S, A, C, pctx, ctx, bf, mask, g2, ldg2, model->va, cc32, Cc,
-                                               ch, Cc, attn_out, srank1, st));
+                                               ch, Cc, attn_out, srank1, scores(S), st));
   if (S2 > 0)
     LAUNCH(MT_KERNEL_ATTENTION, launch_attention(B, K, S2, A, C, pctx2, ctx2, bf, mask2, g2 + A, ldg2, model->va2,
                                                  cc32 ? cc32 + C : nullptr, Cc, ch ? ch + C : nullptr, Cc, nullptr,
-                                                 srank2, st));
+                                                 srank2, scores(S2), st));
   if (taps && taps->c) HIP_TRY(hipMemcpyAsync(taps->c, cc, (size_t)M * Cc * 4, hipMemcpyDeviceToDevice, st));
   // c [W2 | Wt_c] + [b2 | 0]
   GemmProblem p3{};

@@ -424,8 +424,11 @@ int attention_order_max_sentences() { return kOrderMaxB; }
 hipError_t launch_attention(int B, int K, int S, int A, int Cd, const void *P, const void *Cx,
                             int bf16_io, const float *mask, const float *q, int ldq,
                             const float *va, float *ctx_out, int ldc, bf16 *ctx16, int ld16, float *alpha_out,
-                            const int *srank, hipStream_t st) {
+                            const int *srank, float *scores, hipStream_t st) {
   if (B * K == 0) return hipSuccess;
+  if (scores && K > 1 && A >= 512 && attention_beam_ok(B, K, S, A, Cd))
+    return launch_attention_beam(B, K, S, A, Cd, P, Cx, bf16_io, mask, q, ldq, va, ctx_out, ldc, ctx16, ld16, alpha_out,
+                                 scores, st);
   if (bf16_io)
     attn_go<bf16>(B, K, S, A, Cd, (const bf16 *)P, (const bf16 *)Cx, mask, q, ldq, va, ctx_out, ldc, ctx16,
                   ld16, alpha_out, srank, st);

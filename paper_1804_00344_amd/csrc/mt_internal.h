@@ -734,10 +734,16 @@ hipError_t launch_valid_rows(int n, const float *mask, int32_t *idx, int *count,
 // context rows go to ctx_out [M][ldc] fp32 and/or ctx16 [M][ld16] bf16 (either may be NULL);
 // srank (or NULL): the sentences by decreasing length, from launch_attention_order, which only
 // decides the order in which rows are scheduled
+// scores: scratch of B*K*S floats for the beam form (NULL: the row form serves every call)
 hipError_t launch_attention(int B, int K, int S, int A, int Cd, const void *P, const void *Cx,
                             int bf16_io, const float *mask, const float *q, int ldq,
                             const float *va, float *ctx_out, int ldc, bf16 *ctx16, int ld16, float *alpha_out,
-                            const int *srank, hipStream_t st);
+                            const int *srank, float *scores, hipStream_t st);
+// the beam form (mt_attention_beam.hip) and whether it takes these sizes
+bool attention_beam_ok(int B, int K, int S, int A, int Cd);
+hipError_t launch_attention_beam(int B, int K, int S, int A, int Cd, const void *P, const void *Cx, int bf16_io,
+                                 const float *mask, const float *q, int ldq, const float *va, float *ctx_out, int ldc,
+                                 bf16 *ctx16, int ld16, float *alpha_out, float *sc, hipStream_t st);
 // srank[0..B) = the sentences of mask [B][S] by decreasing number of valid positions
 // (B <= attention_order_max_sentences())
 hipError_t launch_attention_order(int B, int S, const float *mask, int *srank, hipStream_t st);

@@ -1,0 +1,67 @@
+"""Attention of several hypotheses per sentence (the beam form): masks with holes, empty
+sentences, tiles of positions at their edges, hypothesis groups, feature counts that are no
+multiple of a wave's 512, and queries and keys beyond the shared-exponential range, against the
+oracle's step (context, weights, state)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1804_00344_amd import synth
+from parity_util import TOL, maxerr, oracle_model, oracle_sentences
+from test_gpu_parity import T, run_step
+
+if torch.cuda.is_available():
+    from paper_1804_00344_amd.runner import Decoder
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def check(gemm, B, K, S, A, H, scale_q=1.0, shift_p=0.0):
+    p = synth.with_sizes(synth.PRESETS["nematus_bf16_ln"], E=32, H=H, A=A, V=64, B=B, K=K, gemm=gemm, layer_norm=False)
+    w = synth.make_weights(p)
+    rng = np.random.default_rng(B * 1000 + K * 10 + S)
+    w["Wa"] = (w["Wa"] * scale_q).astype(np.float32)
+    w["ba"] = (shift_p * rng.standard_normal(A)).astype(np.float32)
+    ctx = synth.round_bf16(np.tanh(rng.standard_normal((B, S, 2 * H))).astype(np.float32))
+    mask = (rng.random((B, S)) < 0.7).astype(np.float32)
+    mask[0] = 1.0
+    if B > 1:
+        mask[B - 1] = 0.0
+    if B > 2 and S > 3:
+        mask[1] = 0.0
+        mask[1, S - 1] = 1.0
+        ctx[1, :S - 1] = np.nan  # padding is never used
+    dec = Decoder.from_preset(p, w)
+    dec.set_batch(ctx, mask, K)
+    dec.precompute()
+    tok, src, state, score = synth.mid_decode_inputs(p)
+    gpu = run_step(dec, p, tok, src, T(state), p.M)
+    torch.cuda.synchronize()
+    orc = oracle_sentences(oracle_model(p, w), K, list(range(B)), np.nan_to_num(ctx), mask, tok, src, state)
+    for b in range(B):
+        rows = slice(b * K, (b + 1) * K)
+        for k, tol in (("alpha", "alpha"), ("c", "tap"), ("state", "state")):
+            err = maxerr(gpu[k][rows].float().cpu().numpy(), orc[b][k])
+            assert err <= TOL[gemm][tol], (b, k, err)
+        assert np.all(gpu["alpha"][rows].cpu().numpy()[:, mask[b] == 0] == 0)
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("B,K,S,A,H", [(3, 2, 1, 512, 64), (2, 3, 300, 512, 64), (2, 9, 70, 512, 64), (5, 4, 9, 528, 272), (4, 5, 65, 1024, 128), (3, 6, 17, 2048, 64),
+                                       (3, 8, 130, 1040, 64), (4, 12, 33, 2064, 128), (3, 13, 24, 4096, 64),
+                                       (2, 16, 7, 512, 144), (700, 3, 16, 512, 64)])
+def test_attention_beam_parity(B, K, S, A, H, gemm):
+    check(gemm, B, K, S, A, H)
+
+
+@pytest.mark.parametrize("scale_q,shift_p", [(40.0, 0.0), (1.0, 12.0), (30.0, 60.0)])
+def test_attention_beam_out_of_range_operands(scale_q, shift_p):
+    """|q| or |P| past the range of the shared exponentials (30 ln2 / 2 = 10.4)."""
+    check("f32", 4, 5, 11, 576, 64, scale_q, shift_p)
+
+
+def test_attention_row_form_still_serves():
+    """Sizes the beam form leaves to the row form: A < 512, and weights beyond its LDS."""
+    check("f32", 3, 4, 12, 496, 64)
+    check("f32", 2, 16, 1024, 512, 64)
