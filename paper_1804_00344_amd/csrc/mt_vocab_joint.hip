@@ -30,11 +30,16 @@ struct VocabJointArgs {
   int cap;
 };
 
-template <typename CT, int HB, int D, bool FIX, int NM>
-__global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(VocabJointArgs a) {
+// G: chunks per workgroup, four runs (waves) each.  The resident rows of several members fill a
+// compute unit's LDS, so one workgroup runs there; with G = 2 it has two waves per SIMD, and
+// one wave's epilogue and operand loads run under the other's MFMAs (two members of 768 rows,
+// V = 50k, bf16: 126 -> 102 us).
+template <typename CT, int HB, int D, bool FIX, int NM, int G>
+__global__ __launch_bounds__((VShape<CT, HB>::NT * G)) void vocab_joint_kernel(VocabJointArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  static_assert(VShape<CT, HB>::NW == 4, "one wave per run");
   constexpr int HBB = VShape<CT, HB>::HBW;
-  constexpr int kVT = VShape<CT, HB>::NT;
+  constexpr int kVT = VShape<CT, HB>::NT * G;
   constexpr int KV = VCfg<CT>::KV;
   constexpr int es = (int)sizeof(CT);
   const int rowb = a.E * es + 16;  // LDS row stride of the resident activations
@@ -42,13 +47,12 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
 
   const int nhb = (a.M + HB - 1) / HB;
   const int L = xcd_remap(blockIdx.x, gridDim.x);
-  const int chunk = L / nhb, hb = L % nhb;
-  if (chunk >= a.n_chunks) return;
+  const int chunk0 = L / nhb * G, hb = L % nhb;
+  if (chunk0 >= a.n_chunks) return;
   const int h0 = hb * HB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int run = wave & 3;
-  const int hc0 = (wave >> 2) * VShape<CT, HB>::WH;
+  const int run = wave & 3, chunk = chunk0 + (wave >> 2);
 
   // ---- resident activations of every member: rows h0..h0+HB-1 (zero beyond M) ----
   {
@@ -70,8 +74,9 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
   const int slots = a.n_chunks * 4;
   const int slot = chunk * 4 + run;
   const int nblk = (a.V + 31) / 32;
-  const int b_begin = (int)((long)nblk * slot / slots);
-  const int b_end = (int)((long)nblk * (slot + 1) / slots);
+  const bool has = chunk < a.n_chunks;  // the last workgroup may lack its second chunk
+  const int b_begin = has ? (int)((long)nblk * slot / slots) : 0;
+  const int b_end = has ? (int)((long)nblk * (slot + 1) / slots) : 0;
   const int npair = (b_end - b_begin) >> 1;
   const int ntile = npair + ((b_end - b_begin) & 1);
   const int KS = a.KS;
@@ -85,7 +90,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
   char *const cbase = (char *)a.cbuf;
 #pragma unroll
   for (int j = 0; j < HBB; ++j) {
-    const int h = h0 + hc0 + j * 32 + lrow;
+    const int h = h0 + j * 32 + lrow;
 #pragma unroll
     for (int mm = 0; mm < NM; ++mm) {
       lm[mm][j] = FIX ? 0.f : -INFINITY;
@@ -95,6 +100,10 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
     loff[j] = (uint32_t)(((size_t)(h < a.M ? h : 0) * a.cap * nlr + chunk * kLists + src) * sizeof(int2));
     lend[j] = loff[j] + (uint32_t)(a.cap - 1) * lstep;
   }
+
+  // the second chunk's waves start about half a tile late, so that the two waves of a SIMD
+  // do not reach their epilogues together
+  if (G > 1 && wave >= 4) __builtin_amdgcn_s_sleep(32);
 
   if (ntile > 0) {
     const int kb = KS * 1024;  // bytes of one 32-row block's fragments
@@ -117,9 +126,10 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
         }
     }
     // activation fragments: member mm, hypothesis block j, k-step ks; the next k-step's are
-    // read before the current step's MFMAs (one wave per SIMD: nothing else covers the LDS
-    // latency)
-    const char *blb = lds + (hc0 + lrow) * rowb + lhalf * (KV / 2 * es);
+    // read before the current step's MFMAs where one wave per SIMD runs and nothing else covers
+    // the LDS latency
+    constexpr bool kPre = G == 1;
+    const char *blb = lds + lrow * rowb + lhalf * (KV / 2 * es);
     auto lds_frag = [&](int ks, v4u(&f)[NM][HBB]) {
 #pragma unroll
       for (int mm = 0; mm < NM; ++mm)
@@ -127,7 +137,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
         for (int j = 0; j < HBB; ++j) f[mm][j] = *(const v4u *)(blb + mm * mbytes + j * 32 * rowb + ks * (KV * es));
     };
     v4u bcur[NM][HBB], bnxt[NM][HBB];
-    lds_frag(0, bcur);
+    if constexpr (kPre) lds_frag(0, bcur);
 
     auto do_tile = [&](auto nbc, int ti) {
       constexpr int NB = decltype(nbc)::value;
@@ -147,57 +157,63 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
       const int tnx = ti + 1 < ntile ? ti + 1 : ti;  // the last tile prefetches itself again
       const int tn = (b_begin + 2 * tnx) * kb;
       const int sec_cur = ti < npair ? kb : 0, sec_nxt = tnx < npair ? kb : 0;
-      for (int ks0 = 0; ks0 < KS; ks0 += D) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          const int ks = ks0 + d;
+      auto kstep = [&](int ks, v4u(&slot)[NM][2]) {
+        if constexpr (kPre) {
           lds_frag(ks + 1 < KS ? ks + 1 : 0, bnxt);
           __builtin_amdgcn_sched_barrier(0);
+        } else {
+          lds_frag(ks, bcur);
+        }
 #pragma unroll
-          for (int mm = 0; mm < NM; ++mm) {
-            const v4u c0 = ring[d][mm][0], c1 = ring[d][mm][1];
-            if constexpr (es == 2) {
-              bf16x8 a0, a1;
-              __builtin_memcpy(&a0, &c0, 16);
-              __builtin_memcpy(&a1, &c1, 16);
+        for (int mm = 0; mm < NM; ++mm) {
+          const v4u c0 = slot[mm][0], c1 = slot[mm][1];
+          if constexpr (es == 2) {
+            bf16x8 a0, a1;
+            __builtin_memcpy(&a0, &c0, 16);
+            __builtin_memcpy(&a1, &c1, 16);
+#pragma unroll
+            for (int j = 0; j < HBB; ++j) {
+              bf16x8 b;
+              __builtin_memcpy(&b, &bcur[mm][j], 16);
+              acc[mm][0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[mm][0][j], 0, 0, 0);
+              if constexpr (NB == 2) acc[mm][1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[mm][1][j], 0, 0, 0);
+            }
+          } else {
+            float fa0[4], fa1[4], fb[HBB][4];
+            __builtin_memcpy(fa0, &c0, 16);
+            __builtin_memcpy(fa1, &c1, 16);
+#pragma unroll
+            for (int j = 0; j < HBB; ++j) __builtin_memcpy(fb[j], &bcur[mm][j], 16);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
               for (int j = 0; j < HBB; ++j) {
-                bf16x8 b;
-                __builtin_memcpy(&b, &bcur[mm][j], 16);
-                acc[mm][0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[mm][0][j], 0, 0, 0);
-                if constexpr (NB == 2) acc[mm][1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[mm][1][j], 0, 0, 0);
+                acc[mm][0][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa0[s], fb[j][s], acc[mm][0][j], 0, 0, 0);
+                if constexpr (NB == 2)
+                  acc[mm][1][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa1[s], fb[j][s], acc[mm][1][j], 0, 0, 0);
               }
-            } else {
-              float fa0[4], fa1[4], fb[HBB][4];
-              __builtin_memcpy(fa0, &c0, 16);
-              __builtin_memcpy(fa1, &c1, 16);
-#pragma unroll
-              for (int j = 0; j < HBB; ++j) __builtin_memcpy(fb[j], &bcur[mm][j], 16);
-#pragma unroll
-              for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int j = 0; j < HBB; ++j) {
-                  acc[mm][0][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa0[s], fb[j][s], acc[mm][0][j], 0, 0, 0);
-                  if constexpr (NB == 2)
-                    acc[mm][1][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa1[s], fb[j][s], acc[mm][1][j], 0, 0, 0);
-                }
-            }
           }
-          // refill this slot with k-step ks + D (the next tile's first k-steps past the end)
-          const bool same = ks + D < KS;
-          const int so = same ? tb + (ks + D) * 1024 : tn + (ks + D - KS) * 1024;
-          const int so2 = so + (same ? sec_cur : sec_nxt);
+        }
+        // refill this slot with k-step ks + D (the next tile's first k-steps past the end)
+        const bool same = ks + D < KS;
+        const int so = same ? tb + (ks + D) * 1024 : tn + (ks + D - KS) * 1024;
+        const int so2 = so + (same ? sec_cur : sec_nxt);
 #pragma unroll
-          for (int mm = 0; mm < NM; ++mm) {
-            ring[d][mm][0] = __builtin_amdgcn_raw_buffer_load_b128(wrs[mm], wvo, so, 0);
-            ring[d][mm][1] = __builtin_amdgcn_raw_buffer_load_b128(wrs[mm], wvo, so2, 0);
-          }
+        for (int mm = 0; mm < NM; ++mm) {
+          slot[mm][0] = __builtin_amdgcn_raw_buffer_load_b128(wrs[mm], wvo, so, 0);
+          slot[mm][1] = __builtin_amdgcn_raw_buffer_load_b128(wrs[mm], wvo, so2, 0);
+        }
+        if constexpr (kPre) {
 #pragma unroll
           for (int mm = 0; mm < NM; ++mm)
 #pragma unroll
             for (int j = 0; j < HBB; ++j) bcur[mm][j] = bnxt[mm][j];
-          __builtin_amdgcn_sched_barrier(0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      for (int ks0 = 0; ks0 < KS; ks0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) kstep(ks0 + d, ring[d]);
       }
 
       // ---- epilogue: biases, member log-sum-exp partials, combined-value candidates ----
@@ -270,32 +286,33 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
   // ---- candidate counts, then each member's 8 log-sum-exp partials per row merged via LDS ----
 #pragma unroll
   for (int j = 0; j < HBB; ++j) {
-    const int h = h0 + hc0 + j * 32 + lrow;
-    if (h < a.M) {
+    const int h = h0 + j * 32 + lrow;
+    if (h < a.M && has) {
       const uint32_t lstart = lend[j] - (uint32_t)(a.cap - 1) * lstep;
       const int n = (int)((loff[j] - lstart) / lstep);
       a.ccnt[((size_t)h * a.n_chunks + chunk) * kLists + src] = n >= a.cap - 1 ? a.cap + 1 : n;
     }
   }
   __syncthreads();  // the resident activations are no longer read
-  float2 *lp = (float2 *)lds;  // [HB][kLists]
+  float2 *lp = (float2 *)lds;  // [chunk][HB][kLists]
 #pragma unroll
   for (int mm = 0; mm < NM; ++mm) {
 #pragma unroll
-    for (int j = 0; j < HBB; ++j) lp[(hc0 + j * 32 + lrow) * kLists + src] = make_float2(lm[mm][j], ls[mm][j]);
+    for (int j = 0; j < HBB; ++j)
+      lp[((wave >> 2) * HB + j * 32 + lrow) * kLists + src] = make_float2(lm[mm][j], ls[mm][j]);
     __syncthreads();
-    for (int hl = tid; hl < HB; hl += kVT) {
-      const int h = h0 + hl;
-      if (h >= a.M) continue;
+    for (int i = tid; i < HB * G; i += kVT) {
+      const int h = h0 + i % HB;
+      if (h >= a.M || chunk0 + i / HB >= a.n_chunks) continue;
       float m = -INFINITY;
-      for (int s = 0; s < kLists; ++s) m = fmaxf(m, lp[hl * kLists + s].x);
+      for (int s = 0; s < kLists; ++s) m = fmaxf(m, lp[i * kLists + s].x);
       float sum = 0.f;
       if (m != -INFINITY)
         for (int s = 0; s < kLists; ++s) {
-          const float2 q = lp[hl * kLists + s];
+          const float2 q = lp[i * kLists + s];
           if (q.x != -INFINITY) sum += q.y * exp_fast(q.x - m);
         }
-      a.part[mm][(size_t)h * a.n_chunks + chunk] = make_float2(m, sum);
+      a.part[mm][(size_t)h * a.n_chunks + chunk0 + i / HB] = make_float2(m, sum);
     }
     __syncthreads();
   }
@@ -304,7 +321,9 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_joint_kernel(Vocab
 // Threshold on the combined values of the first S vocabulary entries: x = sum_m w_m
 // sample_m[v]; the K-th largest of the 64 lane maxima minus the rounding margin, as for a
 // single model.  Block 0 also clears the B sentence arrival counters.
-template <int R>
+// The members' values are requested together (one guarded load after another took 22 us for
+// two members of 768 rows, together 6.6).
+template <int R, int NM>
 __global__ __launch_bounds__(256) void vocab_joint_threshold_kernel(int M, int S, int K, VocabJointSample smp,
                                                                     float *__restrict__ thr, int *scnt, int B) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -312,16 +331,21 @@ __global__ __launch_bounds__(256) void vocab_joint_threshold_kernel(int M, int S
     for (int i = threadIdx.x; i < B; i += 256) __hip_atomic_store(scnt + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int m = blockIdx.x * 4 + w;
   if (m >= M) return;  // uniform per wave
+  float x[NM][R];
+#pragma unroll
+  for (int mm = 0; mm < NM; ++mm) {
+    const float *const row = smp.sample[mm] + (size_t)m * smp.ld;
+#pragma unroll
+    for (int s = 0; s < R; ++s) x[mm][s] = s * 64 + lane < S ? row[s * 64 + lane] : 0.f;
+  }
   uint32_t um[1] = {0u};
 #pragma unroll
   for (int s = 0; s < R; ++s) {
-    const int v = s * 64 + lane;
-    if (v < S) {
-      float x = smp.w[0] * smp.sample[0][(size_t)m * smp.ld + v];
-      for (int mm = 1; mm < smp.n; ++mm) x += smp.w[mm] * smp.sample[mm][(size_t)m * smp.ld + v];
-      const uint32_t c = key_code(x);
-      um[0] = c > um[0] ? c : um[0];
-    }
+    float c = smp.w[0] * x[0][s];
+#pragma unroll
+    for (int mm = 1; mm < NM; ++mm) c += smp.w[mm] * x[mm][s];
+    const uint32_t u = s * 64 + lane < S ? key_code(c) : 0u;
+    um[0] = u > um[0] ? u : um[0];
   }
   float kth = -INFINITY;
   if (wave_count_ge<1>(um, 1, 1u) >= K) kth = key_from_code(wave_kth_code<1>(um, 1, K));
@@ -341,42 +365,50 @@ int vocab_joint_rows(int bf16_mma, int E, int n) {
   return 0;
 }
 
+// chunks per workgroup: two for the bf16 pair of 64-row blocks (their accumulators leave room for
+// two waves per SIMD)
+static int joint_group(int bf16_mma, int HB) { return bf16_mma && HB == 64 ? 2 : 1; }
+
 int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu) {
   const int HB = vocab_joint_rows(bf16_mma, E, n);
   if (HB == 0) return 0;
+  const int G = joint_group(bf16_mma, HB);
   const int nhb = (M + HB - 1) / HB;
   const int tiles = (V + kVRows - 1) / kVRows;
   int c = num_cu / nhb;
   if (c < 1) c = 1;
+  c *= G;
   if (c * 4 > tiles) c = (tiles + 3) / 4;
-  return c;
+  // the workspace holds the single model's chunks; a workgroup without its second chunk is fine
+  const int most = vocab_chunks(bf16_mma, M, V, E, num_cu);
+  return c < most ? c : most;
 }
 
-template <typename CT, int HB, bool FIX, int NM>
+template <typename CT, int HB, bool FIX, int NM, int G>
 static hipError_t vjgo(const VocabJointArgs &a, hipStream_t st) {
-  constexpr int D = NM <= 3 ? 4 : 2;  // ring depth in k-steps (four members: registers)
+  constexpr int D = NM <= 3 && G == 1 ? 4 : 2;  // ring depth in k-steps (registers)
   const int nhb = (a.M + HB - 1) / HB;
   const size_t tbytes = (size_t)NM * HB * (a.E * sizeof(CT) + 16);
-  const size_t lbytes = (size_t)HB * kLists * 8;
+  const size_t lbytes = (size_t)HB * kLists * 8 * G;
   const size_t lds = tbytes > lbytes ? tbytes : lbytes;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)vocab_joint_kernel<CT, HB, D, FIX, NM>,
+    hipError_t e = hipFuncSetAttribute((const void *)vocab_joint_kernel<CT, HB, D, FIX, NM, G>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((vocab_joint_kernel<CT, HB, D, FIX, NM>), dim3(nhb * a.n_chunks), dim3(VShape<CT, HB>::NT), lds,
-                     st, a);
+  hipLaunchKernelGGL((vocab_joint_kernel<CT, HB, D, FIX, NM, G>), dim3(nhb * ((a.n_chunks + G - 1) / G)),
+                     dim3(VShape<CT, HB>::NT * G), lds, st, a);
   return hipGetLastError();
 }
 
 template <typename CT, bool FIX>
 static hipError_t vjgo_n(int n, int HB, const VocabJointArgs &a, hipStream_t st) {
   switch (n) {
-    case 2: return HB == 64 ? vjgo<CT, 64, FIX, 2>(a, st) : vjgo<CT, 32, FIX, 2>(a, st);
-    case 3: return vjgo<CT, 32, FIX, 3>(a, st);
-    default: return vjgo<CT, 32, FIX, 4>(a, st);
+    case 2: return HB == 64 ? vjgo<CT, 64, FIX, 2, sizeof(CT) == 2 ? 2 : 1>(a, st) : vjgo<CT, 32, FIX, 2, 1>(a, st);
+    case 3: return vjgo<CT, 32, FIX, 3, 1>(a, st);
+    default: return vjgo<CT, 32, FIX, 4, 1>(a, st);
   }
 }
 
@@ -415,8 +447,16 @@ hipError_t launch_vocab_joint_threshold(int M, int V, int K, const VocabJointSam
   if (M == 0) return hipSuccess;
   const int S = vocab_sample_size(V);
   const int Sv = V < S ? V : S;  // entries >= V of the sample are padding
-  hipLaunchKernelGGL((vocab_joint_threshold_kernel<kSampleMax / 64>), dim3((M + 3) / 4), dim3(256), 0, st, M, Sv, K,
-                     smp, thr, scnt, B);
+#define MT_JT(NM)                                                                                            \
+  hipLaunchKernelGGL((vocab_joint_threshold_kernel<kSampleMax / 64, NM>), dim3((M + 3) / 4), dim3(256), 0, st, M, Sv, K, \
+                     smp, thr, scnt, B)
+  switch (smp.n) {
+    case 2: MT_JT(2); break;
+    case 3: MT_JT(3); break;
+    case 4: MT_JT(4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef MT_JT
   return hipGetLastError();
 }
 
