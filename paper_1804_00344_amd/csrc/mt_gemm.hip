@@ -15,6 +15,38 @@
 
 namespace mt {
 
+// Stores of one output tile through a buffer view of its rows: a lane past the last column takes
+// an offset beyond the view and rows past the last lie beyond it, so the hardware drops what
+// must not be stored and no store is masked or branched around.  (With a row test and a 64-bit
+// address around each store the epilogue was 12 instructions a store, which a workgroup runs
+// once, from a cold instruction cache: 1024 x 512 x 1024 in 64-row tiles 8.9 -> 8.3 us, in 128-row
+// tiles 15.4 -> 13.9.)
+struct TileOut {
+  __amdgpu_buffer_rsrc_t rs;
+  int rowb;  // bytes per output row
+  __device__ __forceinline__ TileOut(char *out, int bf, int m0, int rows, int ldc)
+      : rs(__builtin_amdgcn_make_buffer_rsrc(out + (size_t)m0 * ldc * (bf ? 2 : 4), 0, rows * ldc * (bf ? 2 : 4), 0x00020000)),
+        rowb(ldc * (bf ? 2 : 4)) {}
+  // offset of column col in the lane's first row of the tile
+  template <bool BF>
+  __device__ __forceinline__ int lane_offset(int row, int col, int N) const {
+    return col < N ? row * rowb + col * (BF ? 2 : 4) : 0x7ffffff0;
+  }
+  // row: further rows (compile-time per store); the whole offset is the lane's, which is what the
+  // range check compares
+  template <bool BF>
+  __device__ __forceinline__ void store(float v, int vo, int row) const {
+    if constexpr (BF) {
+      const bf16 h = to_bf16(v);
+      short x;
+      __builtin_memcpy(&x, &h, 2);
+      __builtin_amdgcn_raw_buffer_store_b16(x, rs, vo + row * rowb, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), rs, vo + row * rowb, 0, 0);
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------------------
 // bf16 operands: weights streamed from global memory straight into registers.
 //
@@ -23,13 +55,19 @@ namespace mt {
 // lane l holding W[ks * 16 + (l / 32) * 8 + j][nb * 32 + l % 32], j < 8 (KSp = K_pad / 16, K_pad a
 // multiple of 128, zero rows beyond K).  One coalesced 16-byte load per lane is one fragment.
 //
-// Block: 32 MB rows x 128 columns, two waves of 32 MB x 64 (MB x 2 blocks of 32x32x16 MFMAs;
-// MB = 1 when 64-row blocks would leave most of the chip idle).  The block's activation rows
+// Block: 32 MB rows x 128 columns (MB by go_wd), four waves: two column halves of 32 MB x 64 (MB x 2
+// blocks of 32x32x16 MFMAs), each shared by two waves.  The block's activation rows
 // pass through LDS in stages of 128 k (bf16, an fp32 operand rounded
 // on the way), double-buffered from two register stages with one barrier per 8 k-steps; each
 // wave's weight fragments come through a register ring refilled D k-steps ahead, so the only
 // LDS traffic is the activations (written once, read by both waves).
-constexpr int kWdCols = 128, kWdThreads = 128;
+//
+// The KW = 2 waves of a column half share its k-steps (of the 8 of a stage, wave kh takes 4), and
+// at the end exchange halves of their partial tiles through LDS, each finishing one 32-column
+// block.  With one wave per column half, 288 tiles of 768 x 3072 left half of the 1024 SIMDs
+// without a wave and the others with nothing to run while one waited: 320 x 3072 x 1024 9.5 -> 8.4
+// us, 768 x 5120 x 1024 17.0 -> 15.6, 1024 x 5120 x 1024 26.9 -> 20.7, 768 x 3584 x 2048 22.9 -> 21.0.
+constexpr int kWdCols = 128, KW = 2, kWdThreads = 128 * KW;
 constexpr int kWdStageK = 128;                   // k per LDS stage (8 k-steps)
 constexpr int kWdRowBytes = kWdStageK * 2 + 16;  // padded LDS row of one stage
 
@@ -37,7 +75,9 @@ template <typename AT, int EPI, int D, int MB>
 __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   constexpr int kWdRows = 32 * MB;
   constexpr int kWdStage = kWdRows * kWdRowBytes;
-  constexpr int RP = 4 * MB;  // staged rows per thread
+  constexpr int RP = 4 * MB / KW;  // staged rows per thread
+  constexpr int SPS = 8 / KW;      // k-steps per stage and wave
+  static_assert(2 * kWdStage >= 4 * MB * 16 * 64 * 4, "the exchange reuses the stages");
   __shared__ __attribute__((aligned(16))) char lds[2 * kWdStage];
   constexpr int AV = (int)sizeof(AT) / 2;  // 16-byte source loads per 8-k vector
   const GemmProblem &P = probs.p[blockIdx.z];
@@ -60,23 +100,32 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   }
   if (m0 >= Mv) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 1);  // column half
+  const int kh = __builtin_amdgcn_readfirstlane(tid >> 7);
 
-  // ---- activation staging: thread t owns 8-k vector c = t % 16 of rows t / 16 + 8 p ----
+  // ---- activation staging: thread t owns 8-k vector c = t % 16 of rows t / 16 + 8 KW p ----
   const int c = tid & 15;
   const char *a_src[RP];
+  {
+    int src[RP];
 #pragma unroll
-  for (int p = 0; p < RP; ++p) {
-    const int m = m0 + (tid >> 4) + 8 * p;
-    int src = m < Mv ? m : 0;  // rows past the count read row 0 and are never stored
-    if (P.a_idx && m < Mv) {
-      src = P.a_idx[m];
-      if (src < 0 || src >= P.a_rows) {
-        if (P.err) atomicOr(P.err, 1 << P.err_bit);
-        src = src < 0 ? 0 : P.a_rows - 1;
-      }
+    for (int p = 0; p < RP; ++p) {
+      const int m = m0 + (tid >> 4) + 8 * KW * p;
+      src[p] = m < Mv ? m : 0;  // rows past the count read row 0 (of the gather) and are never stored
     }
-    a_src[p] = (const char *)P.A + (size_t)src * lda * sizeof(AT);
+    if (P.a_idx) {
+      bool bad = false;
+#pragma unroll
+      for (int p = 0; p < RP; ++p) src[p] = P.a_idx[src[p]];
+#pragma unroll
+      for (int p = 0; p < RP; ++p) {
+        bad |= src[p] < 0 || src[p] >= P.a_rows;
+        src[p] = src[p] < 0 ? 0 : src[p] >= P.a_rows ? P.a_rows - 1 : src[p];
+      }
+      if (bad && P.err) atomicOr(P.err, 1 << P.err_bit);
+    }
+#pragma unroll
+    for (int p = 0; p < RP; ++p) a_src[p] = (const char *)P.A + (size_t)src[p] * lda * sizeof(AT);
   }
   typedef u32x4 StageRegs[RP][AV];
   auto load_stage = [&](int st, StageRegs &R) {
@@ -96,25 +145,27 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
         val = pack_bf16x8(R[p][0], R[p][1]);
       else
         val = R[p][0];
-      *(u32x4 *)(base + ((tid >> 4) + 8 * p) * kWdRowBytes) = val;
+      *(u32x4 *)(base + ((tid >> 4) + 8 * KW * p) * kWdRowBytes) = val;
     }
   };
 
-  // ---- weight fragments: this wave's blocks nb0, nb0 + 1; ring slot of k-step ks is ks % D ----
+  // ---- weight fragments: this wave's blocks nb0, nb0 + 1; ring slot of its n-th k-step is n % D ----
   const int nb0 = (n0 + wave * 64) >> 5;
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
       (void *)P.Bp, 0, ((N + kWdCols - 1) / kWdCols * kWdCols) * KSp * 32, 0x00020000);
   const int wvo = lane * 16;
   const int wb0 = nb0 * KSp * 1024, wstep1 = KSp * 1024;
-  const int kslast = KSp - 1;
   u32x4 ring[D][2];
-  auto fetch = [&](int ks, u32x4(&r)[2]) {
-    const int so = wb0 + (ks < kslast ? ks : kslast) * 1024;  // clamped: in bounds, never used
+  const int nst = KSp / 8;
+  const int last = nst - 1;
+  // the wave's s-th k-step of stage st (past the last: in bounds, never used)
+  auto fetch = [&](int st, int s, u32x4(&r)[2]) {
+    const int so = wb0 + ((st < last ? st : last) * 8 + kh * SPS + s) * 1024;
     r[0] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so, 0);
     r[1] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so + wstep1, 0);
   };
 #pragma unroll
-  for (int d = 0; d < D; ++d) fetch(d, ring[d]);
+  for (int d = 0; d < D; ++d) fetch(d / SPS, d % SPS, ring[d]);
 
   f32x16 acc[MB][2];
 #pragma unroll
@@ -124,33 +175,33 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // 8 k-steps of stage st from LDS buffer buf; the ring slots of stage st are
-  // (8 * (st & 1) + s) % D, static in the two-stage unrolled loop below.  The activation
+  // The wave's k-steps of stage st from LDS buffer buf; the ring slots of stage st are
+  // (SPS * (st & 1) + s) % D, static in the two-stage unrolled loop below.  The activation
   // fragments of k-step s + 1 are read before the MFMAs of k-step s (one wave per SIMD: nothing
   // else would cover the LDS latency).
   const int arow = lane & 31, akoff = (lane >> 5) * 16;
   auto compute = [&](int st, int buf, auto par) {
-    const char *base = lds + buf * kWdStage + arow * kWdRowBytes + akoff;
+    const char *base = lds + buf * kWdStage + arow * kWdRowBytes + akoff + kh * (SPS * 32);
     u32x4 af[MB], an[MB];
 #pragma unroll
     for (int i = 0; i < MB; ++i) af[i] = *(const u32x4 *)(base + i * 32 * kWdRowBytes);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      if (s + 1 < 8) {
+    for (int s = 0; s < SPS; ++s) {
+      if (s + 1 < SPS) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) an[i] = *(const u32x4 *)(base + i * 32 * kWdRowBytes + (s + 1) * 32);
       }
-      u32x4(&slot)[2] = ring[(8 * decltype(par)::value + s) % D];
+      u32x4(&slot)[2] = ring[(SPS * decltype(par)::value + s) % D];
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bitcast16<bf16x8>(af[i]), bitcast16<bf16x8>(slot[j]),
                                                               acc[i][j], 0, 0, 0);
-      fetch(st * 8 + s + D, slot);
+      fetch(st + D / SPS, s, slot);
       // keep each refill right behind the MFMAs that consumed its slot
       __builtin_amdgcn_sched_barrier(0);
-      if (s + 1 < 8) {
+      if (s + 1 < SPS) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) af[i] = an[i];
       }
@@ -160,8 +211,6 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   // Stage st: multiply LDS buffer st & 1, load stage st + 2 into register stage st & 1 and
   // write register stage (st + 1) & 1 (loaded one stage earlier) into the other buffer.
   // Stage indices clamp to the last stage, so the body is branch-free.
-  const int nst = KSp / 8;
-  const int last = nst - 1;
   StageRegs s0, s1;
   load_stage(0, s0);
   load_stage(1 < last ? 1 : last, s1);
@@ -182,17 +231,33 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   if (st < nst) stage(st, s0, s1, std::integral_constant<int, 0>{});
 
   // ---- epilogue: lane holds D[row = 8*(r/4) + 4*(lane/32) + r%4][col = lane % 32] ----
+  // Wave kh finishes column block kh of its half: it leaves the other block's partial sums in LDS
+  // and adds the other wave's to its own (the stages are no longer read: the last one ended in a
+  // barrier).
+  f32x16 fin[MB];
+  {
+    float *const xw = (float *)lds + (wave * 2 + kh) * (MB * 16 * 64) + lane;
+    const float *const xr = (float *)lds + (wave * 2 + (kh ^ 1)) * (MB * 16 * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        xw[(i * 16 + r) * 64] = kh ? acc[i][0][r] : acc[i][1][r];
+        fin[i][r] = kh ? acc[i][1][r] : acc[i][0][r];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) fin[i][r] += xr[(i * 16 + r) * 64];
+  }
+  const int col = n0 + wave * 64 + kh * 32 + (lane & 31);
   const int obf = pin_s(P.out_bf16);
   const float *const biasp = pin_s(P.bias);
   char *const outp = (char *)pin_s(P.out);
   // The bias values are loaded before any store and waited for once: a load between the stores
   // would make every store wait for all earlier stores (the memory counter counts both).
-  float bias[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = n0 + wave * 64 + j * 32 + (lane & 31);
-    bias[j] = biasp ? ((const __attribute__((address_space(1))) float *)biasp)[col < N ? col : N - 1] : 0.f;
-  }
+  const float bias = biasp ? ((const __attribute__((address_space(1))) float *)biasp)[col < N ? col : N - 1] : 0.f;
   // EPI_SCATTER: the output row of each stored row is its (clamped) gather row
   int orow[EPI == EPI_SCATTER ? MB : 1][16];
   if constexpr (EPI == EPI_SCATTER) {
@@ -208,25 +273,32 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
       }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  const TileOut to(outp, obf, m0, Mv - m0 < kWdRows ? Mv - m0 : kWdRows, ldc);
   auto epilogue = [&](auto bf) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wave * 64 + j * 32 + (lane & 31);
-      if (col >= N) continue;
+    constexpr bool BF = decltype(bf)::value;
+    if constexpr (EPI == EPI_SCATTER) {
+      if (col >= N) return;
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m0 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           if (row >= Mv) continue;
-          float v = acc[i][j][r] + bias[j];
-          if (EPI == EPI_TANH) v = tanh_fast(v);
-          int orw = row;
-          if constexpr (EPI == EPI_SCATTER) orw = orow[i][r];
-          if constexpr (decltype(bf)::value)
-            ((__attribute__((address_space(1))) bf16 *)outp)[(size_t)orw * ldc + col] = to_bf16(v);
+          const float v = fin[i][r] + bias;
+          if constexpr (BF)
+            ((__attribute__((address_space(1))) bf16 *)outp)[(size_t)orow[i][r] * ldc + col] = to_bf16(v);
           else
-            ((__attribute__((address_space(1))) float *)outp)[(size_t)orw * ldc + col] = v;
+            ((__attribute__((address_space(1))) float *)outp)[(size_t)orow[i][r] * ldc + col] = v;
+        }
+    } else {
+      const int vo = to.lane_offset<BF>(4 * (lane >> 5), col, N);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float v = fin[i][r] + bias;
+          if (EPI == EPI_TANH) v = tanh_fast(v);
+          to.store<BF>(v, vo, i * 32 + 8 * (r >> 2) + (r & 3));
         }
     }
   };
@@ -244,23 +316,42 @@ static hipError_t go_wd_mb(const Problems &ps, int nprob, hipStream_t st) {
     maxt = t > maxt ? t : maxt;
   }
   if (maxt == 0) return hipSuccess;
-  // ring depth: 16 k-steps when the activation stages leave the registers for it
-  constexpr int D = sizeof(AT) == 2 || MB == 1 ? 16 : 8;
+  constexpr int D = 8;  // ring depth: two stages of a wave's k-steps
   hipLaunchKernelGGL((gemm_wd_kernel<AT, EPI, D, MB>), dim3(maxt, 1, nprob), dim3(kWdThreads), 0, st, ps);
   return hipGetLastError();
 }
 
+// Rows per tile, 32 MB: the fewest rounds of 256 workgroups (one per compute unit), weighted with
+// what a round of such tiles costs.  us for MB = 1, 2, 3, 4 (bf16 rows unless noted): 768 x 5120 x
+// 1024 18.6 15.6 19.5 17.6; 640 x 5120 x 1024 18.1 14.9 19.2 16.8; 768 x 3584 x 2048 24.8 22.4 21.0
+// 24.5; 1024 x 3584 x 2048 32.5 25.0 30.8 25.7; 768 x 3072 x 1024 (fp32 rows) 17.2 17.5 15.8 18.6;
+// 1024 x 3072 x 1024 (fp32 rows) 20.7 18.2 28.6 19.9; 320 x 3072 x 1024 8.4 10.4 13.8 16.8; 512 x
+// 3072 x 1024 12.2 11.2 14.5 17.5.  A unit's L1 delivers the 256 KB of weights and 64 MB KB of
+// activations of a tile (1024 k) at about 47 of its 64 bytes a clock, which is what a round costs.
 template <typename AT, int EPI>
 static hipError_t go_wd(const Problems &ps, int nprob, hipStream_t st) {
-  long t64 = 0;
+  static const double cost[3] = {5.2, 7.0, 10.5};  // of one round, launch excluded
   for (int i = 0; i < nprob; ++i) {
     const GemmProblem &p = ps.p[i];
     if (p.ldb % kWdStageK != 0 || p.K > p.ldb || p.K % 8 != 0) return hipErrorInvalidValue;
-    t64 += (long)((p.M + 63) / 64) * ((p.N + kWdCols - 1) / kWdCols);
   }
-  // 64-row blocks once they cover the chip, else 32-row blocks (twice the blocks, each wave
-  // half the work)
-  return t64 >= 256 ? go_wd_mb<AT, EPI, 2>(ps, nprob, st) : go_wd_mb<AT, EPI, 1>(ps, nprob, st);
+  int best = 1;
+  double bc = 0;
+  for (int mb = 1; mb <= 3; ++mb) {
+    long t = 0;
+    for (int i = 0; i < nprob; ++i)
+      t += (long)((ps.p[i].M + 32 * mb - 1) / (32 * mb)) * ((ps.p[i].N + kWdCols - 1) / kWdCols);
+    const double c = cost[mb - 1] * (double)((t + 255) / 256);
+    if (mb == 1 || c <= bc) {
+      bc = c;
+      best = mb;
+    }
+  }
+  switch (best) {
+    case 1: return go_wd_mb<AT, EPI, 1>(ps, nprob, st);
+    case 2: return go_wd_mb<AT, EPI, 2>(ps, nprob, st);
+    default: return go_wd_mb<AT, EPI, 3>(ps, nprob, st);
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -466,26 +557,37 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
       }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  const TileOut to(outp, obf, m0, Mv - m0 < BLK * TA ? Mv - m0 : BLK * TA, ldc);
   auto epilogue = [&](auto bf) {
+    constexpr bool BF = decltype(bf)::value;
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
       const int col = n0 + BLK * j + lr;
-      if (col >= N) continue;
+      if constexpr (EPI == EPI_SCATTER) {
+        if (col >= N) continue;
 #pragma unroll
-      for (int i = 0; i < TA; ++i)
+        for (int i = 0; i < TA; ++i)
 #pragma unroll
-        for (int r = 0; r < F::NACC; ++r) {
-          const int row = row_of(i, r);
-          if (row >= Mv) continue;
-          float v = acc[i][j][r] + bias[j];
-          if (EPI == EPI_TANH) v = tanh_fast(v);
-          int orw = row;
-          if constexpr (EPI == EPI_SCATTER) orw = orow[i][r];
-          if constexpr (decltype(bf)::value)
-            ((__attribute__((address_space(1))) bf16 *)outp)[(size_t)orw * ldc + col] = to_bf16(v);
-          else
-            ((__attribute__((address_space(1))) float *)outp)[(size_t)orw * ldc + col] = v;
-        }
+          for (int r = 0; r < F::NACC; ++r) {
+            const int row = row_of(i, r);
+            if (row >= Mv) continue;
+            const float v = acc[i][j][r] + bias[j];
+            if constexpr (BF)
+              ((__attribute__((address_space(1))) bf16 *)outp)[(size_t)orow[i][r] * ldc + col] = to_bf16(v);
+            else
+              ((__attribute__((address_space(1))) float *)outp)[(size_t)orow[i][r] * ldc + col] = v;
+          }
+      } else {
+        const int vo = to.lane_offset<BF>(BLK == 16 ? (lane >> 4) * 4 : 4 * (lane >> 5), col, N);
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+          for (int r = 0; r < F::NACC; ++r) {
+            float v = acc[i][j][r] + bias[j];
+            if (EPI == EPI_TANH) v = tanh_fast(v);
+            to.store<BF>(v, vo, BLK * i + (BLK == 16 ? r : 8 * (r >> 2) + (r & 3)));
+          }
+      }
     }
   };
   if (obf)
