@@ -68,28 +68,29 @@ hipError_t launch_enc_lists(int B, int S, const float *mask, const int32_t *tok,
 
 // One position of both directions of a shallow cell: h U, the gates and the new state.
 //
-// A workgroup owns 16 hidden units (their three gate columns) and 32 active rows of one
+// A workgroup owns 16 hidden units (their three gate columns) and 16 RB active rows of one
 // direction; its eight waves split the depth as in gemm_small_kernel (16x16 MFMAs, the
 // activations staged per wave, partial tiles added through LDS in wave order), and thread t
 // finishes one (row, unit) with the three sums it needs, so that the recurrent product is never
-// written and the cell needs no launch of its own.  At 64 sentences and H = 1024 that is 256
+// written and the cell needs no launch of its own.  At 64 sentences (RB = 2) and H = 1024 that is 256
 // workgroups, one on each compute unit; row groups of a unit block are neighbours, so an XCD
 // fetches an eighth of the weights.  What bounds a position is one round of loads behind another
 // (the row list, then the rows' states) and the weights themselves, which every launch fetches
-// anew (25 MB in fp32, 12.6 MB in bf16): in fp32 9 us a position with one sentence, 11.8 with 64
+// anew (25 MB in fp32, 12.6 MB in bf16): in fp32 8 us a position with one sentence, 11.8 with 64
 // of mixed lengths (recurrent product and cell as two launches over all rows: 19.5); in bf16 5 us
 // (two launches: 11).
-constexpr int kEncWaves = 8, kEncThreads = 64 * kEncWaves, kEncRows = 32, kEncUnits = 16, kEncKC = 64;
+constexpr int kEncWaves = 8, kEncThreads = 64 * kEncWaves, kEncUnits = 16, kEncKC = 64;
 
 // FIRST: the first position, with a zero previous state and no product
-template <typename CT, int PK, bool FIRST>
+template <typename CT, int PK, int RB, bool FIRST>
 __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
   constexpr bool BF = sizeof(CT) == 2;
+  constexpr int kEncRows = 16 * RB;              // rows of a workgroup
   constexpr int KSTEP = BF ? 32 : 16;            // k per MFMA operand vector
   constexpr int STEPS = kEncKC / KSTEP;          // k-steps of a chunk
   constexpr int ROWB = kEncKC * (int)sizeof(CT) + 16;
   constexpr int STG = kEncRows * ROWB;           // a wave's chunk
-  constexpr int PER = 3 * 2 * 4 * 64;            // partial sums of a wave: gates x row blocks x 16 x 16
+  constexpr int PER = 3 * RB * 4 * 64;           // partial sums of a wave: gates x row blocks x 16 x 16
   constexpr int LDSB = STG > PER * 4 ? STG : PER * 4;
   __shared__ __attribute__((aligned(16))) char lds[kEncWaves * LDSB];
   const int B = P.B, H = P.H;
@@ -144,16 +145,16 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
   const int cnt = P.acnt[pos];
   if constexpr (!FIRST) load_b(0, b0);
   asm volatile("" : "+v"(carried));  // loaded with the others, not behind the mask
-  if (cb_row < B && cmask == 0.f) *(bits *)(cbase + cb_b * ldc + opos + cb_un) = (bits)carried;
+  if (tid < kEncRows * kEncUnits && cb_row < B && cmask == 0.f) *(bits *)(cbase + cb_b * ldc + opos + cb_un) = (bits)carried;
   if (r0 >= cnt) return;
   const int row_first = __builtin_amdgcn_readfirstlane(arow_raw);  // lane 0: row r0 of the list
   const int arow = ar < cnt ? arow_raw : row_first;
 
   // ---- this thread's (row, unit) of the MFMA output layout, its input gates and state ----
   const int l = tid & 63, rr = (tid >> 6) & 3, ib = tid >> 8;
-  const int lrow = 16 * ib + 4 * (l >> 4) + rr;
+  const int lrow = (16 * ib + 4 * (l >> 4) + rr) % kEncRows;
   const int un = ub * kEncUnits + (l & 15);
-  const bool live = r0 + lrow < cnt;
+  const bool live = tid < kEncRows * kEncUnits && r0 + lrow < cnt;
   const int b = __shfl(arow, lrow, 64);
   const float *const xr = P.xe + ((size_t)b * P.S + pos) * 6 * H + (size_t)dir * 3 * H + un;
 
@@ -181,9 +182,9 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
     h = BF ? P.sst[((size_t)dir * B + b) * H + un] : (float)cbase[b * ldc + oprv + un];
     char *const mine = lds + wave * LDSB;
     typedef __attribute__((__vector_size__(4 * sizeof(float)))) float accv;
-    accv acc[2][3];
+    accv acc[RB][3];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int g = 0; g < 3; ++g) acc[i][g] = accv{0.f, 0.f, 0.f, 0.f};
     const bool two = cnt - r0 > 16;  // the second row block has rows
@@ -209,10 +210,10 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
       for (int d = 0; d < STEPS; ++d) {
         if (c * STEPS + d >= n) break;  // wave-uniform
         const u32x4 a0 = *(const u32x4 *)(frag + d * KSTEP * (int)sizeof(CT));
-        if (two) {
-          const u32x4 a1 = *(const u32x4 *)(frag + 16 * ROWB + d * KSTEP * (int)sizeof(CT));
+        if (RB == 2 && two) {
+          const u32x4 a1 = *(const u32x4 *)(frag + (RB - 1) * 16 * ROWB + d * KSTEP * (int)sizeof(CT));
           mul(0, w[d], a0);
-          mul(1, w[d], a1);
+          mul(RB - 1, w[d], a1);
         } else {
           mul(0, w[d], a0);
         }
@@ -243,15 +244,16 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
 #pragma unroll
     for (int g = 0; g < 3; ++g)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave * PER + ((g * 2 + i) * 4 + r) * 64 + lane] = acc[i][g][r];
+        for (int r = 0; r < 4; ++r) red[wave * PER + ((g * RB + i) * 4 + r) * 64 + lane] = acc[i][g][r];
     __syncthreads();
+    if (!live) return;
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
-      float v = red[g * 512 + tid];
+      float v = red[g * (PER / 3) + tid];
 #pragma unroll
-      for (int w = 1; w < kEncWaves; ++w) v += red[w * PER + g * 512 + tid];
+      for (int w = 1; w < kEncWaves; ++w) v += red[w * PER + g * (PER / 3) + tid];
       us[g] = v;
     }
   }
@@ -264,14 +266,23 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
   if (BF) P.sst[((size_t)dir * B + b) * H + un] = v;
 }
 
+template <typename CT, int PK, int RB>
+static hipError_t go_step_rb(const EncStep &p, hipStream_t st) {
+  const dim3 grid((unsigned)((p.B + 16 * RB - 1) / (16 * RB) * (p.H / kEncUnits) * 2));
+  if (p.first)
+    hipLaunchKernelGGL((enc_step_kernel<CT, PK, RB, true>), grid, dim3(kEncThreads), 0, st, p);
+  else
+    hipLaunchKernelGGL((enc_step_kernel<CT, PK, RB, false>), grid, dim3(kEncThreads), 0, st, p);
+  return hipGetLastError();
+}
+
+// Rows per workgroup: 16 up to 32 sentences, where groups of 32 leave half of the units idle, else
+// 32, which fetch the weights half as often (us for 40 positions with keys and start state, 16 /
+// 32 rows: fp32 32 sentences 495 / 636, 64 865 / 787, 128 1393 / 1269; bf16 64 300 / 270, 128 488 /
+// 465).
 template <typename CT, int PK>
 static hipError_t go_step(const EncStep &p, hipStream_t st) {
-  const dim3 grid((unsigned)((p.B + kEncRows - 1) / kEncRows * (p.H / kEncUnits) * 2));
-  if (p.first)
-    hipLaunchKernelGGL((enc_step_kernel<CT, PK, true>), grid, dim3(kEncThreads), 0, st, p);
-  else
-    hipLaunchKernelGGL((enc_step_kernel<CT, PK, false>), grid, dim3(kEncThreads), 0, st, p);
-  return hipGetLastError();
+  return p.B <= 32 ? go_step_rb<CT, PK, 1>(p, st) : go_step_rb<CT, PK, 2>(p, st);
 }
 
 hipError_t launch_enc_step(int bf16_mma, const EncStep &p, hipStream_t st) {

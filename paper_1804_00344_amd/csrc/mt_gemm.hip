@@ -15,6 +15,20 @@
 
 namespace mt {
 
+// Tile of a problem whose row count is on the device, where a launch for M rows finds a part of
+// them live: each XCD keeps its run of column tiles but walks it row tile by row tile, so that
+// its live tiles come first and are spread over its units one by one.  (Column tile by column
+// tile, the tiles that end at once let the live ones bunch: 1603 valid of 5120 rows x 2048 x 2048
+// in fp32 195 -> 141 us.)  w: the tile's number in launch order, in groups of `per` per workgroup; a
+// permutation of the tiles where their columns divide over the XCDs (otherwise the order stays).
+__device__ __forceinline__ void counted_tile(int w, int tilesM, int tilesN, int per, int &tm, int &tn) {
+  if (tilesN % (kXcds * per) != 0 || (int)gridDim.x * per != tilesM * tilesN) return;
+  const int nx = tilesN / kXcds, g = w / per;  // column tiles of an XCD; workgroup
+  const int x = g % kXcds, i = g / kXcds * per + w % per;
+  tm = i / nx;
+  tn = x * nx + i % nx;
+}
+
 // Stores of one output tile through a buffer view of its rows: a lane past the last column takes
 // an offset beyond the view and rows past the last lie beyond it, so the hardware drops what
 // must not be stored and no store is masked or branched around.  (With a row test and a 64-bit
@@ -89,7 +103,8 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
   const int tilesN = (N + kWdCols - 1) / kWdCols;
   const int tile = xcd_remap(blockIdx.x, gridDim.x);
   if (tile >= tilesM * tilesN) return;
-  const int tm = tile % tilesM, tn = tile / tilesM;  // neighbours share a weight panel
+  int tm = tile % tilesM, tn = tile / tilesM;  // neighbours share a weight panel
+  if (P.m_dev) counted_tile(blockIdx.x, tilesM, tilesN, 1, tm, tn);
   const int m0 = tm * kWdRows, n0 = tn * kWdCols;
   // rows counted on the device, when given, bound the rows read and stored
   const int *const mdp = pin_s(P.m_dev);
@@ -406,7 +421,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
   // a wave without a tile still takes part in the workgroup's barrier below
   const bool has_tile = tile < tilesM * tilesN;
   const int tl = has_tile ? tile : 0;
-  const int tm = tl % tilesM, tn = tl / tilesM;  // neighbours share a weight panel
+  int tm = tl % tilesM, tn = tl / tilesM;  // neighbours share a weight panel
+  if (mdp && has_tile) counted_tile(blockIdx.x * TPB + slot_t, tilesM, tilesN, TPB, tm, tn);
   const int m0 = tm * BLK * TA, n0 = tn * BLK * TB;
   const bool live = has_tile && m0 < Mv;
   // without a split there is no barrier, so a wave without a tile (or whose rows all lie past
