@@ -147,7 +147,7 @@ mt_status check_cfg(const mt_config *c) {
   if (c->enc_layer_norm && c->src_V <= 0) return fail(MT_ERR_ARG, "enc_layer_norm needs an encoder (src_V > 0)");
   if ((c->layer_norm || c->enc_layer_norm) && !(c->ln_eps > 0.f && std::isfinite(c->ln_eps)))
     return fail(MT_ERR_ARG, "ln_eps must be positive and finite");
-  if (vocab_rows_per_block(c->gemm_dtype == MT_BF16, c->E) == 0)
+  if (vocab_rows_per_block(c->gemm_dtype == MT_BF16, c->E, 1) == 0)
     return fail(MT_ERR_SHAPE, "E=%d too large for the vocabulary kernel (E <= %d)", c->E,
                 c->gemm_dtype == MT_BF16 ? 2048 : 1024);
   return MT_OK;

@@ -600,8 +600,9 @@ hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilog
 int gemm_f32_weight_block(long rows, long N, long K);
 
 // ---- vocabulary projection with fused log-sum-exp partials and beam candidates ----
-// hypothesis rows per workgroup (0 if E is too large for the LDS-resident activations)
-int vocab_rows_per_block(int bf16_mma, int E);
+// hypothesis rows per workgroup of a call of M rows (0 if E is too large for the LDS-resident
+// activations)
+int vocab_rows_per_block(int bf16_mma, int E, int M);
 // vocabulary chunks (one workgroup per chunk and row block; per-chunk outputs)
 int vocab_chunks(int bf16_mma, int M, int V, int E, int num_cu);
 int vocab_sample_size(int V);  // vocabulary entries of the threshold pass (padded)

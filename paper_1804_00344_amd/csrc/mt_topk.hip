@@ -24,8 +24,8 @@ namespace mt {
 
 constexpr int kTT = 256;
 constexpr int kRowCap = 4096;          // candidates one row can stage in LDS
+constexpr int kSpec = 4;               // list entries requested with the counts (per sentence)
 constexpr int kSlots = kRowCap / 256;  // register slots per lane when a wave takes a quarter
-constexpr int kSpec = 4;               // list entries requested with the counts
 
 // Row results cross workgroups (and XCDs, whose L2 caches are not coherent with each other)
 // on their way to the sentence merge.  They are written and read with device-scope atomic
@@ -158,8 +158,13 @@ __device__ __forceinline__ void row_rescan(const float *x, int V, int K, float p
 // code, token) in LDS, four waves each select from a quarter and wave 0 merges the quarters.
 // Every workgroup then counts itself in for its sentence; the last of the sentence's K rows
 // merges them.
-template <int KMAX, typename CT>
+// NPL: lists per thread whose counts and first entries are requested together (2, with four
+// entries each, or 8, with one: few rows make many chunks, 1128 to 2048 lists a
+// row, and read list by list 1128 took longer, 12.4 us at 5 rows, than 2048 so, 11.7).
+template <int KMAX, typename CT, int NPL>
 __global__ __launch_bounds__(kTT) void row_select_kernel(RowSelect a) {
+  constexpr int SPEC = NPL == 2 ? 4 : 1;   // list entries requested with the counts
+  constexpr int kNext = NPL == 2 ? 4 : 2;  // and, of a longer list, together after them
   __shared__ __attribute__((aligned(16))) uint32_t su[kRowCap];
   __shared__ __attribute__((aligned(16))) int si[kRowCap];
   __shared__ int wtot[4];
@@ -177,14 +182,14 @@ __global__ __launch_bounds__(kTT) void row_select_kernel(RowSelect a) {
   const bool fused = has_lse || a.comb != nullptr || a.nens > 0;  // lists from the vocabulary pass
   const int *cr = a.cnt ? a.cnt + (size_t)m * nl : nullptr;
 
-  // ---- one round trip for the usual shape (at most one partial and two lists per thread):
-  // the row's log-sum-exp partial, its list fill counts and the first kSpec entries of this
+  // ---- one round trip for the usual shape (at most one partial and NPL lists per thread):
+  // the row's log-sum-exp partial, its list fill counts and the first SPEC entries of this
   // thread's lists are all requested before any of them is needed (lists hold about one entry
   // each; entries past a list's count are loaded and ignored) ----
-  const bool pre = nl <= 2 * kTT && (!has_lse || a.ntiles <= kTT);  // uniform
+  const bool pre = nl <= NPL * kTT && (!has_lse || a.ntiles <= kTT);  // uniform
   float2 pq[4];  // wave 0: partials lane + 64 j
-  int pc[2] = {0, 0};
-  int2 pe[2][kSpec];
+  int pc[NPL] = {};
+  int2 pe[NPL][SPEC];
   if (pre) {
     if (has_lse && w == 0) {
 #pragma unroll
@@ -194,13 +199,13 @@ __global__ __launch_bounds__(kTT) void row_select_kernel(RowSelect a) {
       }
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NPL; ++j) {
       const int l = t + j * kTT;
       if (l < nl) {
         pc[j] = cr ? cr[l] : cap;
         const int2 *e = a.cbuf + (size_t)m * cap * nl + l;  // entry q at e[q * nl]
 #pragma unroll
-        for (int q = 0; q < kSpec; ++q) pe[j][q] = q < cap ? e[(size_t)q * nl] : make_int2(0, -1);
+        for (int q = 0; q < SPEC; ++q) pe[j][q] = q < cap ? e[(size_t)q * nl] : make_int2(0, -1);
       }
     }
   }
@@ -233,7 +238,7 @@ __global__ __launch_bounds__(kTT) void row_select_kernel(RowSelect a) {
     bool over = false;
     if (pre) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < NPL; ++j)
         if (t + j * kTT < nl) {
           over |= pc[j] > cap;
           mine += pc[j] < cap ? pc[j] : cap;
@@ -283,32 +288,32 @@ __global__ __launch_bounds__(kTT) void row_select_kernel(RowSelect a) {
         si[pos] = tok;
       };
       if (pre) {
-        // the first kSpec entries were loaded with the counts; of a longer list the next four
-        // are requested together (one more round trip, not one per entry), the rest one by one
-        int lo[2], lc[2];
+        // the first SPEC entries were loaded with the counts; of a longer list the next
+        // kNext are requested together (one more round trip, not one per entry), the rest one by one
+        int lo[NPL], lc[NPL];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NPL; ++j) {
           const int l = t + j * kTT;
           const int c = l < nl ? (pc[j] < cap ? pc[j] : cap) : 0;
           lo[j] = off;
           lc[j] = c;
 #pragma unroll
-          for (int q = 0; q < kSpec; ++q)
+          for (int q = 0; q < SPEC; ++q)
             if (q < c) stage(off + q, pe[j][q]);
           off += c;
         }
-        int2 ex[2][4];
+        int2 ex[NPL][kNext];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NPL; ++j)
 #pragma unroll
-          for (int q2 = 0; q2 < 4; ++q2)
-            if (kSpec + q2 < lc[j]) ex[j][q2] = a.cbuf[(size_t)m * cap * nl + t + j * kTT + (size_t)(kSpec + q2) * nl];
+          for (int q2 = 0; q2 < kNext; ++q2)
+            if (SPEC + q2 < lc[j]) ex[j][q2] = a.cbuf[(size_t)m * cap * nl + t + j * kTT + (size_t)(SPEC + q2) * nl];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < NPL; ++j) {
 #pragma unroll
-          for (int q2 = 0; q2 < 4; ++q2)
-            if (kSpec + q2 < lc[j]) stage(lo[j] + kSpec + q2, ex[j][q2]);
-          for (int q = kSpec + 4; q < lc[j]; ++q)  // (rarer still)
+          for (int q2 = 0; q2 < kNext; ++q2)
+            if (SPEC + q2 < lc[j]) stage(lo[j] + SPEC + q2, ex[j][q2]);
+          for (int q = SPEC + kNext; q < lc[j]; ++q)  // (rarer still)
             stage(lo[j] + q, a.cbuf[(size_t)m * cap * nl + t + j * kTT + (size_t)q * nl]);
         }
       } else {
@@ -819,13 +824,19 @@ hipError_t launch_row_select(const RowSelect &a, hipStream_t st) {
 #undef MT_SS
     return hipGetLastError();
   }
-#define MT_RS(N)                                                                          \
-  if (a.bf16_mma)                                                                         \
-    hipLaunchKernelGGL((row_select_kernel<N, bf16>), dim3(M), dim3(kTT), 0, st, a);       \
-  else                                                                                    \
-    hipLaunchKernelGGL((row_select_kernel<N, float>), dim3(M), dim3(kTT), 0, st, a);
+  const bool many = a.nl > 2 * kTT;
+#define MT_RS_P(N, CT, P) hipLaunchKernelGGL((row_select_kernel<N, CT, P>), dim3(M), dim3(kTT), 0, st, a)
+#define MT_RS(N)                            \
+  if (a.bf16_mma) {                         \
+    if (many) MT_RS_P(N, bf16, 8);          \
+    else MT_RS_P(N, bf16, 2);               \
+  } else {                                  \
+    if (many) MT_RS_P(N, float, 8);         \
+    else MT_RS_P(N, float, 2);              \
+  }
   MT_KSWITCH(a.K, MT_RS)
 #undef MT_RS
+#undef MT_RS_P
   return hipGetLastError();
 }
 

@@ -63,11 +63,17 @@ struct VocabArgs {
 // KSC > 0: the depth is the compile-time KSC k-steps (E = KSC * KV); each tile's k-loop is
 // then unrolled and the weights are read with buffer loads at a scalar offset (tile base +
 // constant), so a refill costs one scalar add instead of the flat-stream index update.
-template <typename CT, int HB, int D, bool FIX, bool LOG, int KSC>
-__global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a) {
+// NBT: 32-row vocabulary blocks per tile.  2 reuses each activation fragment; 1, with 32 columns per
+// wave, is the form for few rows (at most 64), which is bound by the weights' way in, not by the
+// matrix cores: half the work per wave leaves twice the waves, and the registers saved hold a ring
+// of 32 k-steps, a whole block of bf16 weights at E = 512 (bf16 5 rows x 36001 16.7 -> 12.5 us; fp32 40
+// rows x 50000 47 -> 44, where the padded 64 columns keep the matrix cores busy for 27).
+template <typename CT, int HB, int D, bool FIX, bool LOG, int KSC, int NBT>
+__global__ __launch_bounds__((VShape<CT, HB, 32 * NBT>::NT)) void vocab_kernel(VocabArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int HBB = VShape<CT, HB>::HBW;
-  constexpr int kVT = VShape<CT, HB>::NT;
+  using Shape = VShape<CT, HB, 32 * NBT>;
+  constexpr int HBB = Shape::HBW;
+  constexpr int kVT = Shape::NT;
   constexpr int KV = VCfg<CT>::KV;
   constexpr int es = (int)sizeof(CT);
   const int rowb = a.E * es + 16;  // LDS row stride of the resident activations
@@ -79,8 +85,12 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
   const int h0 = hb * HB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keeps the stream scalar
-  const int run = wave & 3;                                    // vocabulary run of this wave
-  const int hc0 = (wave >> 2) * VShape<CT, HB>::WH;               // first hypothesis column of this wave
+  // vocabulary run and first hypothesis column of this wave; with NBT = 1 the two column groups of
+  // a run lie on neighbouring SIMDs, so that a SIMD's two waves belong to different runs (whose
+  // block counts differ by one)
+  constexpr int NG = Shape::NW / 4;  // column groups
+  const int run = NBT == 1 ? wave / NG : wave & 3;
+  const int hc0 = (NBT == 1 ? wave % NG : wave >> 2) * Shape::WH;
 
   // ---- resident activations: rows h0..h0+HB-1 (zero beyond M) ----
   {
@@ -103,8 +113,8 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
   const int nblk = (a.V + 31) / 32;
   const int b_begin = (int)((long)nblk * slot / slots);
   const int b_end = (int)((long)nblk * (slot + 1) / slots);
-  const int npair = (b_end - b_begin) >> 1;
-  const int ntile = npair + ((b_end - b_begin) & 1);
+  const int npair = NBT == 1 ? b_end - b_begin : (b_end - b_begin) >> 1;  // whole tiles
+  const int ntile = NBT == 1 ? npair : npair + ((b_end - b_begin) & 1);
   const int total = ntile * a.KS;  // flat (tile, k-step) stream, KS % D == 0
   const int KS = a.KS;
   const int lrow = lane & 31, lhalf = lane >> 5;
@@ -134,7 +144,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
   // SIMD would reach their VALU-heavy tile epilogues at the same moments and leave the
   // matrix core idle meanwhile.  Starting the second group about half a tile late puts one
   // wave's epilogue under the other's MFMAs.
-  if (VShape<CT, HB>::NW > 4 && (wave >> 2) == 1) __builtin_amdgcn_s_sleep(32);
+  if (NBT == 2 && Shape::NW > 4 && (wave >> 2) == 1) __builtin_amdgcn_s_sleep(32);
 
   if (ntile > 0) {
     // Weight fragments of step g of tile ti are vocabulary blocks b_begin+2*ti and +1 at
@@ -145,19 +155,19 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
     const v4u *wb = (const v4u *)a.wp + (size_t)b_begin * KS * 64 + lane;
     int pf_k = 0, pf_n = 0, pf_t = 0;
     int poff = 0;  // fragment index of the next prefetch, in 1 KiB steps from wb
-    auto fetch = [&](v4u(&slot)[2]) {
+    auto fetch = [&](v4u(&slot)[NBT]) {
       slot[0] = wb[(size_t)poff * 64];
       // a single-block tile reads its one block twice (the next block may lie past the end)
-      slot[1] = wb[(size_t)(poff + (pf_t < npair ? KS : 0)) * 64];
+      if constexpr (NBT == 2) slot[1] = wb[(size_t)(poff + (pf_t < npair ? KS : 0)) * 64];
       const int more = pf_n + 1 < total ? 1 : 0;
       const int nk = pf_k + more;
       const int wrap = nk == KS ? 1 : 0;
       pf_n += more;
       pf_k = wrap ? 0 : nk;
       pf_t += wrap;
-      poff += more + wrap * KS;
+      poff += more + (NBT == 2 ? wrap * KS : 0);
     };
-    v4u ring[D][2];
+    v4u ring[D][NBT];
     // buffer view of the packed weights (KSC > 0): fixed per-lane offset, scalar fragment
     // offsets.  A tile's second fragment is the next block's; a single-block tile reads its
     // own block again, so no read leaves the run.
@@ -170,7 +180,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
       for (int d = 0; d < D; ++d) {
         const int so = (b_begin * KSC + d) * 1024;
         ring[d][0] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so, 0);
-        ring[d][1] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so + sec0, 0);
+        if constexpr (NBT == 2) ring[d][1] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so + sec0, 0);
       }
     } else {
 #pragma unroll
@@ -182,7 +192,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
     // with period KS).  With one wave per SIMD (fp32) the fragments of the next k-step are
     // read before the current step's MFMAs so the LDS latency is not exposed; bf16 runs two
     // waves per SIMD, which cover it, and has no registers to spare for the second copy.
-    constexpr bool kPrefetchLds = es == 4;
+    constexpr bool kPrefetchLds = es == 4 && NBT == 2;
     auto lds_frag = [&](int ks, v4u(&f)[HBB]) {
 #pragma unroll
       for (int j = 0; j < HBB; ++j) f[j] = bl[(size_t)j * 32 * (rowb / 16) + ks * (KV * es / 16)];
@@ -198,23 +208,23 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
       // With nothing outstanding on entry, the compiler keeps exact, non-draining waits on
       // the ring inside the k-loop.
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-      f32x16 acc[2][HBB];
+      f32x16 acc[NBT][HBB];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NBT; ++i)
 #pragma unroll
         for (int j = 0; j < HBB; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
       // one k-step: MFMAs on ring slot `slot`, then its refill (refill(slot) issues the loads)
-      auto kstep = [&](int ks, v4u(&slot)[2], auto refill) {
+      auto kstep = [&](int ks, v4u(&slot)[NBT], auto refill) {
         if constexpr (kPrefetchLds) {
           lds_frag(ks + 1 < KS ? ks + 1 : 0, bnxt);
           __builtin_amdgcn_sched_barrier(0);  // issue the reads before this step's MFMAs
         } else {
           lds_frag(ks, bcur);
         }
-        const v4u c0 = slot[0], c1 = slot[1];
+        const v4u c0 = slot[0], c1 = slot[NBT - 1];
         if constexpr (es == 2) {
           bf16x8 a0, a1;
           __builtin_memcpy(&a0, &c0, 16);
@@ -224,7 +234,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
             bf16x8 b;
             __builtin_memcpy(&b, &bcur[j], 16);
             acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[0][j], 0, 0, 0);
-            if constexpr (NB == 2) acc[1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[1][j], 0, 0, 0);
+            if constexpr (NB == 2) acc[NBT - 1][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[NBT - 1][j], 0, 0, 0);
           }
         } else {
           float fa0[4], fa1[4], fb[HBB][4];
@@ -237,7 +247,8 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
 #pragma unroll
             for (int j = 0; j < HBB; ++j) {
               acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa0[s], fb[j][s], acc[0][j], 0, 0, 0);
-              if constexpr (NB == 2) acc[1][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa1[s], fb[j][s], acc[1][j], 0, 0, 0);
+              if constexpr (NB == 2)
+                acc[NBT - 1][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa1[s], fb[j][s], acc[NBT - 1][j], 0, 0, 0);
             }
         }
         refill(slot);
@@ -253,16 +264,17 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
       if constexpr (KSC > 0) {
         // byte offsets of this tile's and the next tile's first fragment (the last tile
         // prefetches itself again) and of their second blocks
-        const int tb = (b_begin + 2 * ti) * KSC * 1024;
+        const int tb = (b_begin + NBT * ti) * KSC * 1024;
         const int tnx = ti + 1 < ntile ? ti + 1 : ti;
-        const int tn = (b_begin + 2 * tnx) * KSC * 1024;
+        const int tn = (b_begin + NBT * tnx) * KSC * 1024;
         const int sec_cur = ti < npair ? KSC * 1024 : 0, sec_nxt = tnx < npair ? KSC * 1024 : 0;
 #pragma unroll
         for (int ks = 0; ks < KSC; ++ks)
-          kstep(ks, ring[ks % D], [&](v4u(&r)[2]) {
+          kstep(ks, ring[ks % D], [&](v4u(&r)[NBT]) {
             const int so = ks + D < KSC ? tb + (ks + D) * 1024 : tn + (ks + D - KSC) * 1024;
             r[0] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so, 0);
-            r[1] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so + (ks + D < KSC ? sec_cur : sec_nxt), 0);
+            if constexpr (NBT == 2)
+              r[1] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, so + (ks + D < KSC ? sec_cur : sec_nxt), 0);
           });
       } else {
         for (int ks0 = 0; ks0 < KS; ks0 += D) {
@@ -273,7 +285,7 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
 
       // ---- epilogue of this tile: bias, online log-sum-exp, threshold-filtered candidates ----
       // lane holds rows v = v0 + 32*i + 8*(r/4) + 4*lhalf + r%4 of hypothesis column j*32 + lrow
-      const int v0 = (b_begin + 2 * ti) * 32;
+      const int v0 = (b_begin + NBT * ti) * 32;
 #pragma unroll
       for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -368,8 +380,9 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT)) void vocab_kernel(VocabArgs a
         }
       }
     };
-    for (int ti = 0; ti < npair; ++ti) do_tile(std::integral_constant<int, 2>{}, ti);
-    if (ntile > npair) do_tile(std::integral_constant<int, 1>{}, npair);
+    for (int ti = 0; ti < npair; ++ti) do_tile(std::integral_constant<int, NBT>{}, ti);
+    if constexpr (NBT == 2)
+      if (ntile > npair) do_tile(std::integral_constant<int, 1>{}, npair);
   }  // ntile > 0
 
   if (!collect) return;
@@ -445,9 +458,11 @@ __global__ __launch_bounds__(256) void vocab_threshold_kernel(int M, int S, int 
 
 // ---------------------------------------------------------------------------------------
 
-int vocab_rows_per_block(int bf16_mma, int E) {
+// at most kFewRows hypothesis rows take the one-block tiles
+constexpr int kFewRows = 64;
+int vocab_rows_per_block(int bf16_mma, int E, int M) {
   const int es = bf16_mma ? 2 : 4;
-  const int want = bf16_mma ? 128 : 64;
+  const int want = M <= 32 ? 32 : M <= kFewRows ? 64 : bf16_mma ? 128 : 64;
   for (int hb = want; hb >= 32; hb /= 2)
     if ((size_t)hb * (E * es + 16) <= 160 * 1024 - 1024) return hb;
   return 0;
@@ -494,7 +509,7 @@ static int ring_depth(int bf16_mma, int KS) {
   return KS % 4 == 0 ? 4 : KS % 2 == 0 ? 2 : 1;
 }
 
-template <typename CT, int HB, int D, bool FIX, bool LOG, int KSC>
+template <typename CT, int HB, int D, bool FIX, bool LOG, int KSC, int NBT>
 static hipError_t vgo(const VocabArgs &a, hipStream_t st) {
   const int nhb = (a.M + HB - 1) / HB;
   const size_t tbytes = (size_t)HB * (a.E * sizeof(CT) + 16);
@@ -502,58 +517,68 @@ static hipError_t vgo(const VocabArgs &a, hipStream_t st) {
   const size_t lds = tbytes > lbytes ? tbytes : lbytes;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)vocab_kernel<CT, HB, D, FIX, LOG, KSC>,
+    hipError_t e = hipFuncSetAttribute((const void *)vocab_kernel<CT, HB, D, FIX, LOG, KSC, NBT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((vocab_kernel<CT, HB, D, FIX, LOG, KSC>), dim3(nhb * a.n_chunks), dim3(VShape<CT, HB>::NT), lds,
-                     st, a);
+  hipLaunchKernelGGL((vocab_kernel<CT, HB, D, FIX, LOG, KSC, NBT>), dim3(nhb * a.n_chunks),
+                     dim3(VShape<CT, HB, 32 * NBT>::NT), lds, st, a);
   return hipGetLastError();
 }
 
-template <typename CT, int HB, int D, int KSC>
+template <typename CT, int HB, int D, int KSC, int NBT>
 static hipError_t vgo_k(const VocabArgs &a, hipStream_t st) {
-  if (a.logits) return a.fixed_ref ? vgo<CT, HB, D, true, true, KSC>(a, st) : vgo<CT, HB, D, false, true, KSC>(a, st);
-  return a.fixed_ref ? vgo<CT, HB, D, true, false, KSC>(a, st) : vgo<CT, HB, D, false, false, KSC>(a, st);
+  if (a.logits)
+    return a.fixed_ref ? vgo<CT, HB, D, true, true, KSC, NBT>(a, st) : vgo<CT, HB, D, false, true, KSC, NBT>(a, st);
+  return a.fixed_ref ? vgo<CT, HB, D, true, false, KSC, NBT>(a, st) : vgo<CT, HB, D, false, false, KSC, NBT>(a, st);
 }
 
 // E = 512 (bf16: 32 k-steps, fp32: 64) takes the unrolled form
-template <typename CT, int HB, int D>
+template <typename CT, int HB, int D, int NBT>
 static hipError_t vgo_f(const VocabArgs &a, hipStream_t st) {
-  if (sizeof(CT) == 2 && a.KS == 32 && 32 % D == 0) return vgo_k<CT, HB, D, 32>(a, st);
-  if (sizeof(CT) == 4 && a.KS == 64 && 64 % D == 0) return vgo_k<CT, HB, D, 64>(a, st);
-  return vgo_k<CT, HB, D, 0>(a, st);
+  constexpr int KSC = sizeof(CT) == 2 ? 32 : 64;
+  // few rows: 32 (fp32: 16, more spill) k-steps in flight
+  constexpr int DU = NBT == 2 ? D : sizeof(CT) == 2 ? 32 : 16;
+  if (a.KS == KSC && KSC % D == 0) return vgo_k<CT, HB, DU, KSC, NBT>(a, st);
+  return vgo_k<CT, HB, D, 0, NBT>(a, st);
 }
 
-template <typename CT, int HB>
+template <typename CT, int HB, int NBT>
 static hipError_t vgo_d(const VocabArgs &a, hipStream_t st) {
   switch (ring_depth(sizeof(CT) == 2, a.KS)) {
-    case 8: return vgo_f<CT, HB, 8>(a, st);
-    case 4: return vgo_f<CT, HB, 4>(a, st);
-    case 2: return vgo_f<CT, HB, 2>(a, st);
-    default: return vgo_f<CT, HB, 1>(a, st);
+    case 8: return vgo_f<CT, HB, 8, NBT>(a, st);
+    case 4: return vgo_f<CT, HB, 4, NBT>(a, st);
+    case 2: return vgo_f<CT, HB, 2, NBT>(a, st);
+    default: return vgo_f<CT, HB, 1, NBT>(a, st);
   }
 }
 
-static hipError_t vgo_any(int bf16_mma, const VocabArgs &a, hipStream_t st) {
-  const int HB = vocab_rows_per_block(bf16_mma, a.E);
-  if (bf16_mma) {
-    if (HB == 128) return vgo_d<bf16, 128>(a, st);
-    if (HB == 64) return vgo_d<bf16, 64>(a, st);
-    return vgo_d<bf16, 32>(a, st);
-  }
-  if (HB == 64) return vgo_d<float, 64>(a, st);
-  return vgo_d<float, 32>(a, st);
+template <typename CT>
+static hipError_t vgo_any(const VocabArgs &a, hipStream_t st) {
+  const int HB = vocab_rows_per_block(sizeof(CT) == 2, a.E, a.M);
+  if (a.M <= kFewRows) return HB == 64 ? vgo_d<CT, 64, 1>(a, st) : vgo_d<CT, 32, 1>(a, st);
+  if constexpr (sizeof(CT) == 2)
+    if (HB == 128) return vgo_d<CT, 128, 2>(a, st);
+  if (HB == 64) return vgo_d<CT, 64, 2>(a, st);
+  return vgo_d<CT, 32, 2>(a, st);
 }
 
 int vocab_chunks(int bf16_mma, int M, int V, int E, int num_cu) {
-  const int HB = vocab_rows_per_block(bf16_mma, E);
+  const int HB = vocab_rows_per_block(bf16_mma, E, M);
   const int nhb = (M + HB - 1) / HB;
-  const int tiles = (V + kVRows - 1) / kVRows;
+  const int tiles = (V + kVRows - 1) / kVRows, blocks = (V + 31) / 32;
   int n = num_cu / nhb;
   if (n < 1) n = 1;
-  if (n * 4 > tiles) n = (tiles + 3) / 4;
+  // Few rows: down to one block per wave (a chunk per unit at most), as far as a row's lists stay
+  // within what the selection takes in one round of loads: 64 a wave, or, of a vocabulary large
+  // enough that the weights are worth it, 2048 a workgroup.
+  const int fine = (blocks + 3) / 4, coarse = (tiles + 3) / 4;
+  if (M <= kFewRows && (fine * kLists <= 64 || V >= 8192)) {
+    if (n > fine) n = fine;
+    if (V < 8192 || n * kLists <= 2048) return n;
+  }
+  if (n > coarse) n = coarse;
   return n;
 }
 
@@ -606,7 +631,7 @@ hipError_t launch_vocab(int bf16_mma, const void *t, const void *wp, const float
   a.logits_acc = logits_acc;
   a.cap_stored = logits && cap_stored;
   a.fixed_ref = fixed_ref;
-  return vgo_any(bf16_mma, a, st);
+  return bf16_mma ? vgo_any<bf16>(a, st) : vgo_any<float>(a, st);
 }
 
 }  // namespace mt

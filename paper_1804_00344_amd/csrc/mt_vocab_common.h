@@ -13,11 +13,11 @@ constexpr int kLists = 8;        // candidate buffers per (hypothesis, chunk): 2
 constexpr int kSampleMax = 2048;  // vocabulary entries of the threshold pass
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Hypothesis columns per wave: at most 64 (two 32-column MFMA blocks); a workgroup of HB
-// columns runs HB/64 waves per vocabulary run on the same tiles.
-template <typename CT, int HB>
+// Hypothesis columns per wave: at most WMAX (64: two 32-column MFMA blocks); a workgroup of HB
+// columns runs HB/WH waves per vocabulary run on the same tiles.
+template <typename CT, int HB, int WMAX = 64>
 struct VShape {
-  static constexpr int WH = HB >= 64 ? 64 : HB;  // columns per wave
+  static constexpr int WH = HB >= WMAX ? WMAX : HB;  // columns per wave
   static constexpr int HBW = WH / 32;            // 32-column MFMA blocks per wave
   static constexpr int NW = 4 * (HB / WH);       // waves per workgroup
   static constexpr int NT = 64 * NW;             // threads per workgroup

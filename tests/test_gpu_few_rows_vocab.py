@@ -1,0 +1,52 @@
+"""The vocabulary pass of at most 64 rows (one-block tiles) and the selection from its many lists:
+row counts at the edges of its 32- and 64-column blocks, vocabularies whose block count leaves
+some waves one block more than others or none, both forms of the k-loop, against the oracle's
+log-probabilities and an exhaustive selection."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1804_00344_amd import synth
+from parity_util import TOL, maxerr, oracle_model, oracle_sentences, topk_gap_check
+from test_gpu_parity import T
+
+if torch.cuda.is_available():
+    from paper_1804_00344_amd import mtstep as mt
+    from paper_1804_00344_amd.runner import Decoder
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("E,V,B,K", [(32, 70, 3, 5), (512, 1000, 1, 1), (512, 8191, 2, 16), (512, 8193, 11, 3),
+                                     (512, 40001, 4, 16), (96, 33000, 13, 5), (512, 70000, 8, 8)])
+def test_few_rows_vocabulary_and_selection(E, V, B, K, gemm):
+    p = synth.with_sizes(synth.PRESETS["tiny_bf16_ln"], E=E, H=64, A=64, V=V, B=B, K=K, gemm=gemm)
+    w = synth.make_weights(p, peaked_bias=True)
+    ctx, mask, lens = synth.make_source(p)
+    dec = Decoder.from_preset(p, w)
+    dec.set_batch(ctx, mask, K)
+    dec.precompute()
+    tok, src, state, score = synth.mid_decode_inputs(p)
+    tol = TOL[gemm]["logp"]
+    out = torch.empty((p.M, p.H), device="cuda:0")
+    logp = torch.empty((p.M, V), device="cuda:0")
+    dec.step(T(tok), T(src), T(state), p.M, out, logp=logp)
+    dec.step(T(tok), T(src), T(state), p.M, out)  # the candidates-only form
+    sc, tk, bp, _ = dec.topk(T(score))
+    torch.cuda.synchronize()
+    assert mt.mt_recomputed_rows(dec.model) == 0
+    sents = sorted({0, B - 1})
+    orc = oracle_sentences(oracle_model(p, w), K, sents, ctx, mask, tok, src, state)
+    # exhaustive selection over the GPU's own log-probabilities
+    keys = (T(score)[:, None] + logp).reshape(B, K * V)
+    best = keys.topk(K, 1)[0].reshape(-1)
+    assert float((best - sc).abs().max()) <= 1e-5
+    got = torch.gather(keys, 1, (bp.long() * V + tk.long()).reshape(B, K)).reshape(-1)
+    assert float((got - sc).abs().max()) <= 1e-5
+    for b in sents:
+        rows = slice(b * K, (b + 1) * K)
+        assert maxerr(logp[rows].cpu().numpy(), orc[b]["logp"]) <= tol
+        topk_gap_check(K, score[rows], orc[b]["logp"], sc[rows].cpu().numpy(), tk[rows].cpu().numpy(),
+                       bp[rows].cpu().numpy(), tol)
