@@ -93,15 +93,7 @@ __global__ __launch_bounds__((VShape<CT, HB, 32 * NBT>::NT)) void vocab_kernel(V
   const int hc0 = (NBT == 1 ? wave % NG : wave >> 2) * Shape::WH;
 
   // ---- resident activations: rows h0..h0+HB-1 (zero beyond M) ----
-  {
-    const int vecs_per_row = a.E * es / 16;
-    for (int idx = tid; idx < HB * vecs_per_row; idx += kVT) {
-      const int r = idx / vecs_per_row, c = idx % vecs_per_row;
-      v4u val = {0u, 0u, 0u, 0u};
-      if (h0 + r < a.M) val = *(const v4u *)((const char *)a.t + ((size_t)(h0 + r) * a.E) * es + c * 16);
-      *(v4u *)(lds + r * rowb + c * 16) = val;
-    }
-  }
+  stage_rows<HB, kVT, KSC * 2>(lds, rowb, (const char *)a.t, h0, a.M, a.E * es / 16);
   __syncthreads();
 
   // ---- this wave's contiguous run of vocabulary tiles ----

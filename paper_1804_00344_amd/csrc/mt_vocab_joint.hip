@@ -55,19 +55,9 @@ __global__ __launch_bounds__((VShape<CT, HB>::NT * G)) void vocab_joint_kernel(V
   const int run = wave & 3, chunk = chunk0 + (wave >> 2);
 
   // ---- resident activations of every member: rows h0..h0+HB-1 (zero beyond M) ----
-  {
-    const int vpr = a.E * es / 16;
 #pragma unroll
-    for (int mm = 0; mm < NM; ++mm) {
-      const char *src = (const char *)a.t[mm];
-      for (int idx = tid; idx < HB * vpr; idx += kVT) {
-        const int r = idx / vpr, c = idx % vpr;
-        v4u val = {0u, 0u, 0u, 0u};
-        if (h0 + r < a.M) val = *(const v4u *)(src + ((size_t)(h0 + r) * a.E) * es + c * 16);
-        *(v4u *)(lds + mm * mbytes + r * rowb + c * 16) = val;
-      }
-    }
-  }
+  for (int mm = 0; mm < NM; ++mm)
+    stage_rows<HB, kVT, 0>(lds + mm * mbytes, rowb, (const char *)a.t[mm], h0, a.M, a.E * es / 16);
   __syncthreads();
 
   // ---- this wave's run of vocabulary tiles (as in the single-model kernel) ----
