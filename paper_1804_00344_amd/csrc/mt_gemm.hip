@@ -735,8 +735,9 @@ static hipError_t go_f32(const Problems &ps, int nprob, hipStream_t st) {
 //    products at 64 rows (384) 8.5 / 6.9 and at 96 (576) 8.7 / 9.0;
 //  * fp32 in the 32-column packing, whose tiles are the coarser ones, 896: context at 5 rows 38.5
 //    / 7.9, at 128 (896) 39.6 / 29.1, at 256 40.0 / 45.9;
-//  * fp32 in the 16-column packing, 256: recurrent at 32 rows (192) 7.1 / 6.7, readout at 256
-//    (256) 6.8 / 6.2, but s1 at 5 rows (320) 6.7 / 8.1 and two recurrent products at 5 (384) 7.2 / 8.2.
+//  * fp32 in the 16-column packing, 256 up to 32 rows, else 512: recurrent at 32 rows (192) 7.1 / 6.7,
+//    at 64 (384) 10.6 / 9.8, sample at 128 (512) 8.0 / 6.0, but s1 at 5 rows (320) 6.7 / 8.1 and at 40
+//    (640) 10.8 / 13.1, two recurrent products at 5 (384) 7.2 / 8.2.
 static bool small_rows(int bf16_mma, const Problems &ps, int nprob) {
   long wg = 0;
   for (int i = 0; i < nprob; ++i) {
@@ -744,7 +745,7 @@ static bool small_rows(int bf16_mma, const Problems &ps, int nprob) {
     if (p.K % 16 != 0 || p.M < 1 || p.wblk != ps.p[0].wblk) return false;
     wg += (long)((p.M + 31) / 32) * ((p.N + (bf16_mma ? 31 : 15)) / (bf16_mma ? 32 : 16));
   }
-  return wg <= (bf16_mma ? 512 : ps.p[0].wblk == 32 ? 896 : 256);
+  return wg <= (bf16_mma ? 512 : ps.p[0].wblk == 32 ? 896 : ps.p[0].M > 32 ? 512 : 256);
 }
 
 hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilogue epi, hipStream_t st) {
