@@ -269,9 +269,17 @@ WsLayout ws_layout(const mt_model *m, int B, int K) {
   L.kc = K;
   L.sample = take(M * vocab_sample_size(c.V) * 4);
   L.thr = take(M * 4);
-  L.part = take(M * L.ntiles * sizeof(float2));
-  L.cbuf = take(M * L.ntiles * vocab_lists() * kVocabCap * sizeof(int2));
-  L.ccnt = take(M * L.ntiles * vocab_lists() * sizeof(int));
+  // Few rows take more chunks each (vocab_chunks), up to twice the lists of the next larger row
+  // count: a workspace sized for more rows holds the lists of 32 and of 64 rows too, so that a
+  // program that sizes it for its largest batch can pass it to the smaller ones.
+  size_t lists = M * L.ntiles;
+  for (size_t few = 32; few <= 64 && few < M; few *= 2) {
+    const size_t n = few * vocab_chunks(m->bf16, (int)few, c.V, c.E, m->num_cu);
+    lists = n > lists ? n : lists;
+  }
+  L.part = take(lists * sizeof(float2));
+  L.cbuf = take(lists * vocab_lists() * kVocabCap * sizeof(int2));
+  L.ccnt = take(lists * vocab_lists() * sizeof(int));
   L.lse = take(M * 4);
   L.rowc = take(M * K * sizeof(int2));
   // chunks of a materialised row for the first selection level

@@ -127,7 +127,8 @@ __global__ __launch_bounds__(512) void attn_score_kernel(int K, int S, int A, in
       qmax = fmaxf(qmax, fabsf(x));
       eq[k][e] = __builtin_amdgcn_exp2f(x);
     }
-  // NaN compares as out of range here and below: the plain form then gives what it always gave
+  // an infinity is out of range here and below, as is a finite value past the limit (the plain form);
+  // the maxima pass over a NaN, which makes the sum NaN in either form
   const bool qok = __ballot(!(qmax <= kExpLim)) == 0;
   vs = wave_sum(vs);
   if (lane == 0) vpart[wave] = vs;

@@ -50,3 +50,28 @@ def test_few_rows_vocabulary_and_selection(E, V, B, K, gemm):
         assert maxerr(logp[rows].cpu().numpy(), orc[b]["logp"]) <= tol
         topk_gap_check(K, score[rows], orc[b]["logp"], sc[rows].cpu().numpy(), tk[rows].cpu().numpy(),
                        bp[rows].cpu().numpy(), tol)
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+def test_workspace_of_more_rows_holds_few_rows(gemm):
+    """A workspace sized for more than 64 rows is large enough for every smaller batch, whose rows
+    take more lists each, and a step of 60 rows in one of 65 rows gives what its own gives."""
+    p = synth.with_sizes(synth.PRESETS["tiny_bf16_ln"], E=32, H=64, A=64, V=36001, B=12, K=5, gemm=gemm)
+    w = synth.make_weights(p, peaked_bias=True)
+    ctx, mask, lens = synth.make_source(p)
+    dec = Decoder.from_preset(p, w)
+    small = [mt.mt_workspace_bytes(dec.model, b, 1, 8) for b in range(1, 65)]
+    assert max(small) <= min(mt.mt_workspace_bytes(dec.model, b, 1, 8) for b in range(65, 200))
+    res = []
+    for B in (p.B, p.B + 1):
+        dec.set_batch(ctx, mask, p.K)
+        dec.ws = torch.zeros(mt.mt_workspace_bytes(dec.model, B, p.K, dec.S), dtype=torch.uint8, device="cuda:0")
+        dec.precompute()
+        tok, src, state, score = synth.mid_decode_inputs(p)
+        out = torch.empty((p.M, p.H), device="cuda:0")
+        dec.step(T(tok), T(src), T(state), p.M, out)
+        sc, tk, bp, _ = dec.topk(T(score))
+        torch.cuda.synchronize()
+        res.append([x.cpu().numpy().copy() for x in (out, sc, tk, bp)])
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
