@@ -425,9 +425,9 @@ def main():
         torch.cuda.synchronize()
         e_s = (time.perf_counter() - t0) / reps
         rec["encode"] = {
-            "what": "mt_encode of the batch: bi-directional GRU over the padded source (one input product, then "
-                    "per position the recurrent products of both directions and two cells, then per "
-                    "transition block one more product and two more cells)",
+            "what": "mt_encode of the batch: bi-directional GRU over the source (one input product over the valid "
+                    "positions, then per position one kernel of both directions for a shallow cell; for other cells a "
+                    "product and a cell launch per block)",
             "src_V": args.encode, "enc_transitions": args.enc_transitions, "enc_layer_norm": args.enc_layer_norm, "padded_S": int(dec.S), "ms_per_batch": round(1e3 * e_s, 3),
             "src_tokens_per_s": round(float(lens.sum()) / e_s, 1),
             "per_decoder_step_us_at_precompute_interval": round(1e6 * e_s / p.steps, 2),
