@@ -11,6 +11,8 @@
 // padding of the packed weights (finite x 0 adds nothing).  Epilogues load the bias before any
 // store and read the problem fields into scalar registers once: a load between the stores
 // would make every store wait for all earlier ones (the memory counter counts both).
+#include <algorithm>
+
 #include "mt_gemm_common.h"
 
 namespace mt {
@@ -396,7 +398,8 @@ struct F32Form {
   static constexpr int HALF = 64 / BLK;     // lane groups of the k quadruples
 };
 
-template <int BLK, int TA, int TB, int S, int EPI, int D, int U>
+// WIDE: rows by 64-bit addresses instead of a buffer view, whose offsets have 32 bits (go_f32).
+template <int BLK, int TA, int TB, int S, int EPI, int D, int U, bool WIDE = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
   using F = F32Form<BLK>;
   typedef __attribute__((__vector_size__(F::NACC * sizeof(float)))) float accv;
@@ -433,10 +436,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
   const int ks_begin = part * (KSp / S), ks_end = ks_begin + KSp / S;
 
   // activation rows of this lane (gathered, clamped; rows past M read row 0, never stored), as
-  // byte offsets into a buffer view of A
+  // byte offsets into a buffer view of A (at most 2^32 - 1 bytes)
   const __amdgpu_buffer_rsrc_t ars =
-      __builtin_amdgcn_make_buffer_rsrc((void *)P.A, 0, P.a_rows * lda * 4, 0x00020000);
-  int a_off[TA];
+      __builtin_amdgcn_make_buffer_rsrc((void *)P.A, 0, (int)((uint32_t)P.a_rows * (uint32_t)lda * 4u), 0x00020000);
+  typename std::conditional<WIDE, const char *, uint32_t>::type a_off[TA];
 #pragma unroll
   for (int i = 0; i < TA; ++i) {
     const int m = m0 + BLK * i + lr;
@@ -448,7 +451,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
         src = src < 0 ? 0 : P.a_rows - 1;
       }
     }
-    a_off[i] = src * lda * 4;
+    if constexpr (WIDE) a_off[i] = (const char *)P.A + (size_t)src * lda * 4;
+    else a_off[i] = (uint32_t)src * (uint32_t)lda * 4u;
   }
   // the view covers the column blocks that exist (the packing pads N further, to N_pad, but a
   // tile may reach past even that): fragments of blocks beyond N read as zero and their
@@ -468,7 +472,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Problems probs) {
     int k = kc * F::KSTEP + lk;
     k = k < K ? k : K - 4;  // past K: the row's last vector (it meets zero weights)
 #pragma unroll
-    for (int i = 0; i < TA; ++i) r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ars, a_off[i] + k * 4, 0, 0);
+    for (int i = 0; i < TA; ++i) {
+      if constexpr (WIDE) r.a[i] = *(const u32x4 *)(a_off[i] + (size_t)k * 4);
+      else r.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ars, (int)(a_off[i] + (uint32_t)k * 4u), 0, 0);
+    }
 #pragma unroll
     for (int j = 0; j < TB; ++j) r.b[j] = __builtin_amdgcn_raw_buffer_load_b128(wrs, wvo, wb0 + (j * KSp + kc) * 1024, 0);
   };
@@ -686,10 +693,24 @@ int gemm_f32_weight_block(long rows, long N, long K) {
   return (c32 >= 0 && c32 < c16) ? 32 : 16;
 }
 
+// Rows that span 4 GiB or more (a large batch's context, states or embeddings) lie beyond what the
+// buffer view's 32-bit offsets reach: one tile shape of each form with 64-bit row addresses.
+template <int BLK, int TA, int TB, int EPI>
+static hipError_t go_f32_wide(const Problems &ps, int nprob, hipStream_t st) {
+  long maxw = 0;
+  for (int i = 0; i < nprob; ++i)
+    maxw = std::max(maxw, (long)((ps.p[i].M + BLK * TA - 1) / (BLK * TA)) * ((ps.p[i].N + BLK * TB - 1) / (BLK * TB)));
+  if (maxw == 0) return hipSuccess;
+  hipLaunchKernelGGL((gemm_f32_kernel<BLK, TA, TB, 1, EPI, 4, 4, true>), dim3((unsigned)((maxw + 3) / 4), 1, nprob),
+                     dim3(256), 0, st, ps);
+  return hipGetLastError();
+}
+
 template <int EPI>
 static hipError_t go_f32(const Problems &ps, int nprob, hipStream_t st) {
   const int blk = ps.p[0].wblk == 32 ? 32 : 16;
   int minsteps = 1 << 30;
+  bool wide = false;
   long rows[2], cols[2];
   for (int i = 0; i < nprob; ++i) {
     const GemmProblem &p = ps.p[i];
@@ -699,7 +720,9 @@ static hipError_t go_f32(const Problems &ps, int nprob, hipStream_t st) {
     minsteps = steps < minsteps ? steps : minsteps;
     rows[i] = p.M;
     cols[i] = p.N;
+    wide = wide || (unsigned long long)p.a_rows * p.lda * 4 > 0xffffffffull;
   }
+  if (wide) return blk == 32 ? go_f32_wide<32, 2, 2, EPI>(ps, nprob, st) : go_f32_wide<16, 3, 3, EPI>(ps, nprob, st);
   int bi = 0;
   if (f32_best(blk, rows, cols, nprob, minsteps, &bi) < 0) return hipErrorInvalidValue;
   if (blk == 32) {
