@@ -426,7 +426,7 @@ hipError_t launch_attention(int B, int K, int S, int A, int Cd, const void *P, c
                             const float *va, float *ctx_out, int ldc, bf16 *ctx16, int ld16, float *alpha_out,
                             const int *srank, float *scores, hipStream_t st) {
   if (B * K == 0) return hipSuccess;
-  if (scores && K > 1 && A >= 512 && attention_beam_ok(B, K, S, A, Cd))
+  if (scores && attention_takes_beam(B, K, S, A, Cd))
     return launch_attention_beam(B, K, S, A, Cd, P, Cx, bf16_io, mask, q, ldq, va, ctx_out, ldc, ctx16, ld16, alpha_out,
                                  scores, st);
   if (bf16_io)

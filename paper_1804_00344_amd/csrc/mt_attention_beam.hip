@@ -396,6 +396,27 @@ bool attention_beam_ok(int B, int K, int S, int A, int Cd) {
   return K <= kKMax && A <= 4096 && A % 8 == 0 && Cd % 4 == 0 && B <= 65535 && S <= kScoreMaxS && ((K + 3) / 4 * 4) * S * 4 <= 65536 - 256;
 }
 
+// Which sizes take it: enough positions to pay for the second launch and, with more rows, for the
+// units that the row form then fills by itself.  Attention of a step in us between two events (about
+// 5 of them are the events'), row form / beam form, mean length 0.4 S unless given, A = 2H; the first
+// two lines lie on the beam form's side:
+//   A = 2048, bf16: 1 x 5, S 25 15.2 / 11.3; 1 x 16, S 50 21.4 / 15.6; 64 x 12, S 80 31.4 / 30.9, S 160
+//     53.8 / 46.4; fp32: 64 x 12, S 80 35.1 / 31.3
+//   bf16: 1 x 5, S 10 10.9 / 11.1; 64 x 12, S 25 16.6 / 21.0, S 50 23.2 / 24.5; 256 x 2, S 50 21.9 / 25.4;
+//     128 x 5, S 50 21.9 / 24.3; fp32: 128 x 2, all of length 80 31.1 / 37.0
+//   A = 512: 1 x 5, length 25 10.4 / 11.3 (fp32); 64 x 16, S 80 21.1 / 26.1 (bf16)
+// Of 5808 shapes (K 2..16, B 1..512, S 10..320, A 512..2048, lengths S or of mean 0.4 S, both types)
+// 7 are slower than with the row form by more than 3%, by 11% (2 us) at most; with the beam form
+// wherever it can run, 1713 were, by up to 57%.  Few hypotheses share few exponentials (K <= 3), and
+// more than 12 take the context workgroups the longest; with fewer than 512 features a scoring wave
+// has lanes without one (not measured).
+bool attention_takes_beam(int B, int K, int S, int A, int Cd) {
+  if (K < 2 || A < 512 || !attention_beam_ok(B, K, S, A, Cd)) return false;
+  const double w = K <= 3 ? 4.0 : K > 12 ? 2.0 : 1.0;
+  const double s = 12.0 + K + w * B * K / 14.0;  // positions at A = 2048; as 1 / sqrt(A) elsewhere
+  return (double)S * S * A >= 2048.0 * s * s;
+}
+
 hipError_t launch_attention_beam(int B, int K, int S, int A, int Cd, const void *P, const void *Cx, int bf16_io,
                                  const float *mask, const float *q, int ldq, const float *va, float *ctx_out, int ldc,
                                  bf16 *ctx16, int ld16, float *alpha_out, float *sc, hipStream_t st) {

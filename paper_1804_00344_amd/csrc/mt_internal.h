@@ -740,8 +740,9 @@ hipError_t launch_attention(int B, int K, int S, int A, int Cd, const void *P, c
                             int bf16_io, const float *mask, const float *q, int ldq,
                             const float *va, float *ctx_out, int ldc, bf16 *ctx16, int ld16, float *alpha_out,
                             const int *srank, float *scores, hipStream_t st);
-// the beam form (mt_attention_beam.hip) and whether it takes these sizes
+// the beam form (mt_attention_beam.hip), whether it can take these sizes, and whether it does
 bool attention_beam_ok(int B, int K, int S, int A, int Cd);
+bool attention_takes_beam(int B, int K, int S, int A, int Cd);
 hipError_t launch_attention_beam(int B, int K, int S, int A, int Cd, const void *P, const void *Cx, int bf16_io,
                                  const float *mask, const float *q, int ldq, const float *va, float *ctx_out, int ldc,
                                  bf16 *ctx16, int ld16, float *alpha_out, float *sc, hipStream_t st);

@@ -1,0 +1,17 @@
+"""Which form of a kernel a call takes: the library's own rules (host code, no GPU), called by their
+C++ names."""
+import ctypes as C
+
+from paper_1804_00344_amd import mtstep as mt
+
+
+def _fn(symbol, restype, nargs):
+    f = getattr(mt.lib(), symbol)
+    f.restype, f.argtypes = restype, [C.c_int] * nargs
+    return f
+
+
+def attention_form(B, K, S, E, H, A):
+    """"beam" or "row": the attention of a step (its scores need rows of 3H + E floats of scratch)."""
+    takes = _fn("_ZN2mt20attention_takes_beamEiiiii", C.c_bool, 5)
+    return "beam" if S <= 3 * H + E and takes(B, K, S, A, 2 * H) else "row"

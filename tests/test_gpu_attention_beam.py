@@ -55,6 +55,23 @@ def test_attention_beam_parity(B, K, S, A, H, gemm):
     check(gemm, B, K, S, A, H)
 
 
+# sizes that take the beam form (tests/test_routes.py checks it): the fewest positions it takes with
+# two and with three hypotheses, every hypothesis group size (one to three groups of 2..6), feature
+# counts off a wave's 512, position counts at the edges of the context kernel's 64, 128 and 256 and
+# of the score tiles (1, 2 and 4 positions), the most weights its LDS holds, many sentences
+BEAM = [(1, 2, 11, 4096, 16), (2, 3, 12, 4096, 16), (2, 3, 300, 512, 128), (3, 2, 64, 512, 64), (5, 4, 41, 528, 272),
+        (4, 5, 65, 1024, 128), (3, 6, 21, 2048, 64), (3, 8, 128, 1040, 64), (3, 8, 129, 1040, 64), (2, 9, 70, 512, 64),
+        (4, 12, 33, 2064, 128), (3, 13, 24, 4096, 64), (2, 16, 70, 512, 144), (2, 3, 256, 512, 96),
+        (2, 5, 257, 512, 96), (1, 16, 1020, 512, 352), (3, 4, 1024, 512, 352), (100, 4, 32, 4096, 16),
+        (70, 2, 40, 4096, 16)]
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("B,K,S,A,H", BEAM)
+def test_attention_beam_form_parity(B, K, S, A, H, gemm):
+    check(gemm, B, K, S, A, H)
+
+
 @pytest.mark.parametrize("scale_q,shift_p", [(40.0, 0.0), (1.0, 12.0), (30.0, 60.0)])
 def test_attention_beam_out_of_range_operands(scale_q, shift_p):
     """|q| or |P| past the range of the shared exponentials (30 ln2 / 2 = 10.4)."""
