@@ -1139,14 +1139,15 @@ static mt_status ensemble_topk_joint(int n, mt_model *const *models, const float
   const int M = B * K, V = c.V, E = c.E, bf = model->bf16;
   if (n < 2 || n > kJointMax || vocab_joint_rows(bf, E, n) == 0)
     return fail(MT_ERR_SHAPE, "the joint vocabulary pass does not support %d members at E=%d", n, E);
-  const int nj = vocab_joint_chunks(bf, M, V, E, n, model->num_cu);
+  int group = 1;
+  const int nj = vocab_joint_chunks(bf, M, V, E, n, model->num_cu, &group);
   const WsLayout L0 = ws_layout(model, B, K);
   char *W0 = (char *)ws[0];
   VocabJointSample smp{};
   smp.n = n;
   smp.ld = vocab_sample_size(V);
   VocabJoint vj{};
-  vj.n = n; vj.bf16_mma = bf; vj.M = M; vj.V = V; vj.E = E; vj.n_chunks = nj; vj.cap = kVocabCap;
+  vj.n = n; vj.bf16_mma = bf; vj.M = M; vj.V = V; vj.E = E; vj.n_chunks = nj; vj.group = group; vj.cap = kVocabCap;
   vj.fixed_ref = 1;
   EnsembleConst ec{};
   ec.n = n;

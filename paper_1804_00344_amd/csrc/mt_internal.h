@@ -649,9 +649,10 @@ hipError_t launch_ensemble_const(const EnsembleConst &a, int M, hipStream_t st);
 // hypothesis rows per workgroup of the joint pass (0: not supported for this E, type and n)
 int vocab_joint_rows(int bf16_mma, int E, int n);
 // vocabulary chunks of the joint pass (<= vocab_chunks of the same model: its workspace holds them)
-int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu);
+// (group: chunks per workgroup)
+int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu, int *group);
 struct VocabJoint {
-  int n, bf16_mma, M, V, E, n_chunks, cap, fixed_ref;
+  int n, bf16_mma, M, V, E, n_chunks, group, cap, fixed_ref;
   const void *t[kJointMax];      // [M][E] readout activations per member
   const void *wp[kJointMax];     // packed Wo^T per member (vocab_pack_host layout)
   const float *bias[kJointMax];  // padded output bias per member

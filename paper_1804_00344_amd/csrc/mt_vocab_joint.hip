@@ -32,8 +32,8 @@ struct VocabJointArgs {
 
 // G: chunks per workgroup, four runs (waves) each.  The resident rows of several members fill a
 // compute unit's LDS, so one workgroup runs there; with G = 2 it has two waves per SIMD, and
-// one wave's epilogue and operand loads run under the other's MFMAs (two members of 768 rows,
-// V = 50k, bf16: 126 -> 102 us).
+// one wave's epilogue and operand loads run under the other's MFMAs (which sizes take it, and the
+// figures: vocab_joint_chunks).
 template <typename CT, int HB, int D, bool FIX, int NM, int G>
 __global__ __launch_bounds__((VShape<CT, HB>::NT * G)) void vocab_joint_kernel(VocabJointArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -370,23 +370,41 @@ int vocab_joint_rows(int bf16_mma, int E, int n) {
   return 0;
 }
 
-// chunks per workgroup: two for the bf16 pair of 64-row blocks (their accumulators leave room for
-// two waves per SIMD)
-static int joint_group(int bf16_mma, int HB) { return bf16_mma && HB == 64 ? 2 : 1; }
-
-int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu) {
-  const int HB = vocab_joint_rows(bf16_mma, E, n);
-  if (HB == 0) return 0;
-  const int G = joint_group(bf16_mma, HB);
+// Chunks of a call with `group` of them per workgroup
+static int joint_chunks(int bf16_mma, int HB, int group, int M, int V, int E, int num_cu) {
   const int nhb = (M + HB - 1) / HB;
   const int tiles = (V + kVRows - 1) / kVRows;
   int c = num_cu / nhb;
   if (c < 1) c = 1;
-  c *= G;
+  c *= group;
   if (c * 4 > tiles) c = (tiles + 3) / 4;
   // the workspace holds the single model's chunks; a workgroup without its second chunk is fine
   const int most = vocab_chunks(bf16_mma, M, V, E, num_cu);
   return c < most ? c : most;
+}
+
+// Two chunks per workgroup (bf16 pairs of 64-row blocks, whose accumulators leave room for two waves
+// per SIMD) where that shortens the waves' runs enough.  With b1 and b2 32-row blocks per wave in the
+// two forms, a block of a SIMD shared by two waves takes 1.6 times as long as one alone, and the
+// shallower ring and the larger workgroup cost 5 to 7 us a launch.  us between two events, one / two
+// chunks (E = 512): 5 rows x 10000 19.9 / 28.0, x 50000 28.4 / 32.3, x 85000 39.2 / 44.7 (b2 = b1:
+// only the grid is halved); 64 rows x 50000 32.6 / 33.3; 128 x 50000 (4 blocks, 2) 37.7 / 33.4; 160 x
+// 50000 (5, 4) 41.7 / 47.6; 320 x 50000 (8, 5) 60.5 / 62.9; 512 x 50000 (13, 7) 84.0 / 76.7; 768 x
+// 50000 (19, 10) 115.7 / 104.7; E = 128: 320 x 20000 (4, 2) 21.0 / 22.2, 768 x 85000 95.4 / 77.7.  Of
+// 663 sizes (E 128, 256, 512, 5 to 1024 rows, V 500 to 85000) the line takes the slower form by more
+// than 3% in 6, by 8% at most.
+int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu, int *group) {
+  *group = 1;
+  const int HB = vocab_joint_rows(bf16_mma, E, n);
+  if (HB == 0) return 0;
+  const int c1 = joint_chunks(bf16_mma, HB, 1, M, V, E, num_cu);
+  if (!bf16_mma || HB != 64) return c1;
+  const int c2 = joint_chunks(bf16_mma, HB, 2, M, V, E, num_cu);
+  const int blocks = (V + 31) / 32;
+  const int b1 = (blocks + 4 * c1 - 1) / (4 * c1), b2 = (blocks + 4 * c2 - 1) / (4 * c2);
+  if (b1 - 1.6 * b2 < 0.35 + 112.0 / E) return c1;
+  *group = 2;
+  return c2;
 }
 
 template <typename CT, int HB, bool FIX, int NM, int G>
@@ -409,17 +427,20 @@ static hipError_t vjgo(const VocabJointArgs &a, hipStream_t st) {
 }
 
 template <typename CT, bool FIX>
-static hipError_t vjgo_n(int n, int HB, const VocabJointArgs &a, hipStream_t st) {
+static hipError_t vjgo_n(int n, int HB, int group, const VocabJointArgs &a, hipStream_t st) {
+  if constexpr (sizeof(CT) == 2)
+    if (group == 2) return n == 2 && HB == 64 ? vjgo<CT, 64, FIX, 2, 2>(a, st) : hipErrorInvalidValue;
+  if (group != 1) return hipErrorInvalidValue;
   switch (n) {
-    case 2: return HB == 64 ? vjgo<CT, 64, FIX, 2, sizeof(CT) == 2 ? 2 : 1>(a, st) : vjgo<CT, 32, FIX, 2, 1>(a, st);
+    case 2: return HB == 64 ? vjgo<CT, 64, FIX, 2, 1>(a, st) : vjgo<CT, 32, FIX, 2, 1>(a, st);
     case 3: return vjgo<CT, 32, FIX, 3, 1>(a, st);
     default: return vjgo<CT, 32, FIX, 4, 1>(a, st);
   }
 }
 
 template <typename CT>
-static hipError_t vjgo_ct(int n, int HB, bool fix, const VocabJointArgs &a, hipStream_t st) {
-  return fix ? vjgo_n<CT, true>(n, HB, a, st) : vjgo_n<CT, false>(n, HB, a, st);
+static hipError_t vjgo_ct(const VocabJoint &j, int HB, const VocabJointArgs &a, hipStream_t st) {
+  return j.fixed_ref ? vjgo_n<CT, true>(j.n, HB, j.group, a, st) : vjgo_n<CT, false>(j.n, HB, j.group, a, st);
 }
 
 hipError_t launch_vocab_joint(const VocabJoint &j, hipStream_t st) {
@@ -444,7 +465,7 @@ hipError_t launch_vocab_joint(const VocabJoint &j, hipStream_t st) {
   a.cbuf = j.cbuf;
   a.ccnt = j.ccnt;
   a.cap = j.cap;
-  return j.bf16_mma ? vjgo_ct<bf16>(j.n, HB, j.fixed_ref, a, st) : vjgo_ct<float>(j.n, HB, j.fixed_ref, a, st);
+  return j.bf16_mma ? vjgo_ct<bf16>(j, HB, a, st) : vjgo_ct<float>(j, HB, a, st);
 }
 
 hipError_t launch_vocab_joint_threshold(int M, int V, int K, const VocabJointSample &smp, float *thr, int *scnt,

@@ -15,3 +15,15 @@ def attention_form(B, K, S, E, H, A):
     """"beam" or "row": the attention of a step (its scores need rows of 3H + E floats of scratch)."""
     takes = _fn("_ZN2mt20attention_takes_beamEiiiii", C.c_bool, 5)
     return "beam" if S <= 3 * H + E and takes(B, K, S, A, 2 * H) else "row"
+
+
+def joint_chunks(E, V, M, n=2, bf16=1, num_cu=256):
+    """(chunks, chunks per workgroup) of the joint vocabulary pass."""
+    f = mt.lib()._ZN2mt18vocab_joint_chunksEiiiiiiPi
+    f.restype, f.argtypes = C.c_int, [C.c_int] * 6 + [C.POINTER(C.c_int)]
+    group = C.c_int(0)
+    return f(bf16, M, V, E, n, num_cu, C.byref(group)), group.value
+
+
+def vocab_chunks(E, V, M, bf16=1, num_cu=256):
+    return _fn("_ZN2mt12vocab_chunksEiiiii", C.c_int, 5)(bf16, M, V, E, num_cu)

@@ -1,8 +1,9 @@
 """The rules that choose a kernel's form by the sizes of a call (host code, no GPU)."""
 import pytest
 
-from routes import attention_form
+from routes import attention_form, joint_chunks, vocab_chunks
 from test_gpu_attention_beam import BEAM
+from test_gpu_joint_pairs import PAIRS
 
 NEMATUS = dict(E=512, H=1024, A=2048)
 
@@ -27,3 +28,31 @@ def test_attention_beam_cases_take_the_beam_form(B, K, S, A, H):
 ])
 def test_attention_form(B, K, S, dims, form):
     assert attention_form(B, K, S, **dims) == form
+
+
+@pytest.mark.parametrize("E,V,B,K", PAIRS)
+def test_joint_pair_cases_take_two_chunks(E, V, B, K):
+    assert joint_chunks(E, V, B * K)[1] == 2
+
+
+def test_joint_pair_cases_have_odd_chunk_counts():
+    assert [joint_chunks(E, V, B * K)[0] % 2 for E, V, B, K in (PAIRS[1], PAIRS[-1])] == [1, 1]
+
+
+@pytest.mark.parametrize("E", [64, 128, 256, 512])
+@pytest.mark.parametrize("V", [500, 1000, 10000, 30000, 50000, 85000])
+def test_joint_pair_of_few_rows_keeps_one_chunk_per_workgroup(E, V):
+    """Up to 64 rows are one row block: two chunks per workgroup would only halve the workgroups."""
+    for M in (1, 5, 20, 40, 64):
+        n, group = joint_chunks(E, V, M)
+        assert group == 1 and n == min(256, (V + 255) // 256)
+
+
+def test_joint_chunks_fit_the_single_models_workspace():
+    for E, V, M in ((512, 50000, 768), (512, 50000, 160), (512, 85000, 320), (128, 1000, 5), (512, 72001, 320)):
+        assert joint_chunks(E, V, M)[0] <= vocab_chunks(E, V, M)
+    assert joint_chunks(512, 50000, 768)[1] == 2
+    # another type, another number of members, 32-row blocks: one chunk
+    assert joint_chunks(512, 50000, 768, bf16=0)[1] == 1
+    assert joint_chunks(512, 50000, 768, n=3)[1] == 1
+    assert joint_chunks(1024, 50000, 768)[1] == 1
