@@ -64,7 +64,7 @@ struct VocabArgs {
 // then unrolled and the weights are read with buffer loads at a scalar offset (tile base +
 // constant), so a refill costs one scalar add instead of the flat-stream index update.
 // NBT: 32-row vocabulary blocks per tile.  2 reuses each activation fragment; 1, with 32 columns per
-// wave, is the form for few rows (at most 64), which is bound by the weights' way in, not by the
+// wave, is the form for few rows (at most 64: one_block_tiles), which is bound by the weights' way in, not by the
 // matrix cores: half the work per wave leaves twice the waves, and the registers saved hold a ring
 // of 32 k-steps, a whole block of bf16 weights at E = 512 (bf16 5 rows x 36001 16.7 -> 12.5 us; fp32 40
 // rows x 50000 47 -> 44, where the padded 64 columns keep the matrix cores busy for 27).
@@ -546,10 +546,21 @@ static hipError_t vgo_d(const VocabArgs &a, hipStream_t st) {
   }
 }
 
+// Whether a call takes the one-block tiles.  Rows wider than 2 KB leave a unit's LDS room for one
+// workgroup, one wave per SIMD: nothing covers the LDS reads of a one-block tile there, so a wave of
+// several blocks is better off with tiles of two (us at 1 row, two-block / one-block tiles: bf16 E = 2048
+// of 33000 37.4 / 44.2, E = 1536 of 33000 32.1 / 36.6; 40 rows of 85000 E = 2048 84.8 / 89.8, fp32 E =
+// 1024 142.7 / 151.9; 1 row of 50000 E = 2048 48.9 / 45.8), while one block a wave halves its chain (1 row of
+// 20000: bf16 E = 2048 31.6 / 29.0, fp32 E = 1024 58.1 / 40.4).
+static bool one_block_tiles(int M, int V, int row_bytes, int n_chunks) {
+  return M <= kFewRows && (row_bytes <= 2048 || (V + 31) / 32 <= 4 * n_chunks);
+}
+
 template <typename CT>
 static hipError_t vgo_any(const VocabArgs &a, hipStream_t st) {
   const int HB = vocab_rows_per_block(sizeof(CT) == 2, a.E, a.M);
-  if (a.M <= kFewRows) return HB == 64 ? vgo_d<CT, 64, 1>(a, st) : vgo_d<CT, 32, 1>(a, st);
+  if (one_block_tiles(a.M, a.V, a.E * (int)sizeof(CT), a.n_chunks))
+    return HB == 64 ? vgo_d<CT, 64, 1>(a, st) : vgo_d<CT, 32, 1>(a, st);
   if constexpr (sizeof(CT) == 2)
     if (HB == 128) return vgo_d<CT, 128, 2>(a, st);
   if (HB == 64) return vgo_d<CT, 64, 2>(a, st);
@@ -562,14 +573,17 @@ int vocab_chunks(int bf16_mma, int M, int V, int E, int num_cu) {
   const int tiles = (V + kVRows - 1) / kVRows, blocks = (V + 31) / 32;
   int n = num_cu / nhb;
   if (n < 1) n = 1;
-  // Few rows: down to one block per wave (a chunk per unit at most), as far as a row's lists stay
-  // within what the selection takes in one round of loads: 64 a wave, or, of a vocabulary large
-  // enough that the weights are worth it, 2048 a workgroup.
   const int fine = (blocks + 3) / 4, coarse = (tiles + 3) / 4;
-  if (M <= kFewRows && (fine * kLists <= 64 || V >= 8192)) {
-    if (n > fine) n = fine;
-    if (V < 8192 || n * kLists <= 2048) return n;
-  }
+  const int fn = n < fine ? n : fine;
+  const int row = E * (bf16_mma ? 2 : 4);
+  // Few rows: down to one block per wave (a chunk per unit at most), while a row's lists stay within
+  // what the selection takes in one round of loads: 64 a wave, or, of more than 2048 entries or of
+  // wider rows, 2048 a workgroup.  us of the pass and the selection, two-block chunks / these: 1 x 1 of
+  // 2000 fp32 E = 512 30.2 / 21.9, of 8000 30.0 / 22.9; 4 x 16 of 2000 52.0 / 36.6; bf16 E = 512 8 x 2 of
+  // 2000 17.7 / 18.1, 5 x 12 25.5 / 23.2, 1 x 5 of 8000 21.2 / 19.9; but E = 64 8 x 2 of 2000 15.6 / 16.9,
+  // where few lists (K > 1) are selected by sentence.
+  const bool lists = fine * kLists <= 64 || ((V > 2048 || row >= 256) && fn * kLists <= 2048);
+  if (M <= kFewRows && lists && one_block_tiles(M, V, row, fn)) return fn;
   if (n > coarse) n = coarse;
   return n;
 }

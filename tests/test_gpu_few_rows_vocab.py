@@ -22,6 +22,20 @@ pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not torch.cuda.is_available(),
 @pytest.mark.parametrize("E,V,B,K", [(32, 70, 3, 5), (512, 1000, 1, 1), (512, 8191, 2, 16), (512, 8193, 11, 3),
                                      (512, 40001, 4, 16), (96, 33000, 13, 5), (512, 70000, 8, 8)])
 def test_few_rows_vocabulary_and_selection(E, V, B, K, gemm):
+    check(gemm, E, V, B, K)
+
+
+# one block per wave below 8192 entries, with lists for the per-row selection; rows wider than 2 KB with
+# one block per wave and with tiles of two (a last tile of one block among them)
+@pytest.mark.parametrize("gemm,E,V,B,K", [("f32", 512, 3000, 4, 16), ("bf16", 512, 2049, 5, 12), ("bf16", 64, 2000, 8, 2),
+                                          ("f32", 32, 5001, 2, 5), ("f32", 1024, 33001, 13, 5), ("f32", 768, 3000, 1, 5),
+                                          ("f32", 1024, 20000, 3, 11), ("bf16", 2048, 9000, 3, 11),
+                                          ("bf16", 1536, 33057, 1, 5), ("bf16", 2048, 33000, 11, 5)])
+def test_few_rows_chunk_rules(gemm, E, V, B, K):
+    check(gemm, E, V, B, K)
+
+
+def check(gemm, E, V, B, K):
     p = synth.with_sizes(synth.PRESETS["tiny_bf16_ln"], E=E, H=64, A=64, V=V, B=B, K=K, gemm=gemm)
     w = synth.make_weights(p, peaked_bias=True)
     ctx, mask, lens = synth.make_source(p)

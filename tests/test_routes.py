@@ -56,3 +56,19 @@ def test_joint_chunks_fit_the_single_models_workspace():
     assert joint_chunks(512, 50000, 768, bf16=0)[1] == 1
     assert joint_chunks(512, 50000, 768, n=3)[1] == 1
     assert joint_chunks(1024, 50000, 768)[1] == 1
+
+
+@pytest.mark.parametrize("bf16,E,V,M,chunks", [
+    # one block per wave where the lists allow it, whatever the vocabulary
+    (1, 512, 1000, 1, 8), (1, 512, 2000, 1, 16), (1, 512, 8000, 40, 63), (0, 512, 8000, 64, 63), (1, 512, 50000, 5, 256),
+    (0, 64, 2000, 1, 16), (1, 64, 2049, 1, 17),
+    # a narrow row and a small vocabulary: few lists, selected by sentence
+    (1, 64, 2000, 1, 8), (1, 64, 1000, 1, 8),
+    # rows wider than 2 KB: one block per wave or tiles of two
+    (1, 2048, 32768, 32, 256), (1, 2048, 33000, 32, 129), (1, 1536, 85000, 32, 256), (1, 2048, 16384, 33, 128),
+    (1, 2048, 20000, 33, 79), (0, 1024, 32768, 5, 256), (0, 1024, 33000, 5, 129), (1, 1024, 33000, 5, 256),
+    # more rows: tiles of two
+    (1, 512, 8000, 65, 32), (0, 512, 50000, 65, 128),
+])
+def test_vocab_chunks(bf16, E, V, M, chunks):
+    assert vocab_chunks(E, V, M, bf16) == chunks
