@@ -315,7 +315,7 @@ mt_status mt_set_state_reuse(mt_model *model, int on);
 
 /* 1 if the joint vocabulary pass supports these n members (2 <= n <= 4, single-source, equal V,
  * E and gemm dtype, the members' readout activations of one row block fitting one workgroup's
- * LDS together), else 0.  models: HOST array. */
+ * LDS together, V*E output weights below 4 GiB), else 0.  models: HOST array. */
 int mt_ensemble_joint_ok(int n, mt_model *const *models);
 
 /* Translation bookkeeping after mt_beam_topk of step `step` (batched beam search decoding

@@ -1137,7 +1137,7 @@ static mt_status ensemble_topk_joint(int n, mt_model *const *models, const float
   mt_model *model = models[0];  // profiling slot
   const mt_config &c = model->cfg;
   const int M = B * K, V = c.V, E = c.E, bf = model->bf16;
-  if (n < 2 || n > kJointMax || vocab_joint_rows(bf, E, n) == 0)
+  if (n < 2 || n > kJointMax || vocab_joint_rows(bf, V, E, n) == 0)
     return fail(MT_ERR_SHAPE, "the joint vocabulary pass does not support %d members at E=%d", n, E);
   int group = 1;
   const int nj = vocab_joint_chunks(bf, M, V, E, n, model->num_cu, &group);
@@ -1214,7 +1214,7 @@ int mt_ensemble_joint_ok(int n, mt_model *const *models) {
         models[i]->bf16 != models[0]->bf16)
       return 0;
   }
-  return vocab_joint_rows(models[0]->bf16, models[0]->cfg.E, n) > 0 ? 1 : 0;
+  return vocab_joint_rows(models[0]->bf16, models[0]->cfg.V, models[0]->cfg.E, n) > 0 ? 1 : 0;
 }
 
 mt_status mt_ensemble_step(mt_model *model, int member, int n_members, float weight, int B, int K, int S,
@@ -1231,7 +1231,7 @@ mt_status mt_ensemble_step(mt_model *model, int member, int n_members, float wei
   if (!(weight != 0.f && std::isfinite(weight))) return fail(MT_ERR_ARG, "weight must be finite and nonzero");
   if (comb_logits) {
     CHECK(check_dev_ptr(comb_logits, "comb_logits", 4));
-  } else if (vocab_joint_rows(model->bf16, model->cfg.E, n_members) == 0) {
+  } else if (vocab_joint_rows(model->bf16, model->cfg.V, model->cfg.E, n_members) == 0) {
     return fail(MT_ERR_SHAPE, "the joint vocabulary pass does not support %d members at E=%d (%s): pass comb_logits",
                 n_members, model->cfg.E, model->bf16 ? "bf16" : "fp32");
   }

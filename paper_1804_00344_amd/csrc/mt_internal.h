@@ -608,6 +608,7 @@ int vocab_chunks(int bf16_mma, int M, int V, int E, int num_cu);
 int vocab_sample_size(int V);  // vocabulary entries of the threshold pass (padded)
 int vocab_lists();             // candidate buffers per (row, chunk)
 size_t vocab_pack_bytes(int bf16_mma, int V, int E);
+bool vocab_fits_view(int bf16_mma, int V, int E);
 // packs Wo^T rows into MFMA fragment order; src is Wo [E][V] or, if src_is_emb, emb [V][E]
 void vocab_pack_host(int bf16_mma, int V, int E, const float *src, int src_is_emb, void *out);
 // thr[m] = a value reached by K of sample[m][0 .. min(V, S)) (the K-th largest of 64 lane maxima),
@@ -646,8 +647,8 @@ struct EnsembleConst {
 hipError_t launch_ensemble_const(const EnsembleConst &a, int M, hipStream_t st);
 
 // ---- fused ensemble: one vocabulary pass for 2..kJointMax members (same V, E and type) ----
-// hypothesis rows per workgroup of the joint pass (0: not supported for this E, type and n)
-int vocab_joint_rows(int bf16_mma, int E, int n);
+// hypothesis rows per workgroup of the joint pass (0: not supported for this V, E, type and n)
+int vocab_joint_rows(int bf16_mma, int V, int E, int n);
 // vocabulary chunks of the joint pass (<= vocab_chunks of the same model: its workspace holds them)
 // (group: chunks per workgroup)
 int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu, int *group);

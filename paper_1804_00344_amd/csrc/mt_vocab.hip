@@ -465,6 +465,10 @@ size_t vocab_pack_bytes(int bf16_mma, int V, int E) {
   return (size_t)Vpad * E * (bf16_mma ? 2 : 4);
 }
 
+// Weights of 4 GiB or more lie beyond what a buffer view's 32-bit offsets reach: the flat form of the
+// k-loop serves them, and no joint pass
+bool vocab_fits_view(int bf16_mma, int V, int E) { return vocab_pack_bytes(bf16_mma, V, E) <= 0xffffffffull; }
+
 int vocab_sample_size(int V) {
   const int s = V < kSampleMax ? V : kSampleMax;
   return (s + kVRows - 1) / kVRows * kVRows;
@@ -526,13 +530,14 @@ static hipError_t vgo_k(const VocabArgs &a, hipStream_t st) {
   return a.fixed_ref ? vgo<CT, HB, D, true, false, KSC, NBT>(a, st) : vgo<CT, HB, D, false, false, KSC, NBT>(a, st);
 }
 
-// E = 512 (bf16: 32 k-steps, fp32: 64) takes the unrolled form
+// E = 512 (bf16: 32 k-steps, fp32: 64) takes the unrolled form, through a buffer view
 template <typename CT, int HB, int D, int NBT>
 static hipError_t vgo_f(const VocabArgs &a, hipStream_t st) {
   constexpr int KSC = sizeof(CT) == 2 ? 32 : 64;
   // few rows: 32 (fp32: 16, more spill) k-steps in flight
   constexpr int DU = NBT == 2 ? D : sizeof(CT) == 2 ? 32 : 16;
-  if (a.KS == KSC && KSC % D == 0) return vgo_k<CT, HB, DU, KSC, NBT>(a, st);
+  if (a.KS == KSC && KSC % D == 0 && vocab_fits_view(sizeof(CT) == 2, a.V, a.E))
+    return vgo_k<CT, HB, DU, KSC, NBT>(a, st);
   return vgo_k<CT, HB, D, 0, NBT>(a, st);
 }
 

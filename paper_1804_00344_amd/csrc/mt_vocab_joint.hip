@@ -359,8 +359,8 @@ __global__ __launch_bounds__(256) void vocab_joint_threshold_kernel(int M, int S
 
 // ---------------------------------------------------------------------------------------
 
-int vocab_joint_rows(int bf16_mma, int E, int n) {
-  if (n < 2 || n > kJointMax) return 0;
+int vocab_joint_rows(int bf16_mma, int V, int E, int n) {
+  if (n < 2 || n > kJointMax || !vocab_fits_view(bf16_mma, V, E)) return 0;
   const int es = bf16_mma ? 2 : 4;
   const int KV = bf16_mma ? 16 : 8;
   if (E % (4 * KV) != 0) return 0;  // the ring is 4 k-steps deep and the k-loop steps by 4
@@ -395,7 +395,7 @@ static int joint_chunks(int bf16_mma, int HB, int group, int M, int V, int E, in
 // than 3% in 6, by 8% at most.
 int vocab_joint_chunks(int bf16_mma, int M, int V, int E, int n, int num_cu, int *group) {
   *group = 1;
-  const int HB = vocab_joint_rows(bf16_mma, E, n);
+  const int HB = vocab_joint_rows(bf16_mma, V, E, n);
   if (HB == 0) return 0;
   const int c1 = joint_chunks(bf16_mma, HB, 1, M, V, E, num_cu);
   if (!bf16_mma || HB != 64) return c1;
@@ -445,7 +445,7 @@ static hipError_t vjgo_ct(const VocabJoint &j, int HB, const VocabJointArgs &a, 
 
 hipError_t launch_vocab_joint(const VocabJoint &j, hipStream_t st) {
   if (j.M == 0) return hipSuccess;
-  const int HB = vocab_joint_rows(j.bf16_mma, j.E, j.n);
+  const int HB = vocab_joint_rows(j.bf16_mma, j.V, j.E, j.n);
   if (HB == 0) return hipErrorInvalidValue;
   VocabJointArgs a{};
   for (int m = 0; m < j.n; ++m) {

@@ -78,6 +78,63 @@ def test_attention_beam_out_of_range_operands(scale_q, shift_p):
     check("f32", 4, 5, 11, 576, 64, scale_q, shift_p)
 
 
+# operands beyond the shared-exponential range, in both types: everywhere, in one feature (infinite
+# once scaled), at one position of one sentence, in one hypothesis beside others in range, and a
+# hypothesis of NaN beside finite ones
+EXTREMES = ["queries", "keys", "feature", "position", "hypothesis", "nan"]
+EXTREME_SIZES = dict(B=4, K=5, S=44, A=1040, H=64)
+
+
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("where", EXTREMES)
+def test_attention_beam_extremes_match_the_row_form(where, gemm):
+    """The same hypotheses as sentences of one hypothesis each run the row form on the same keys and
+    queries: weights and contexts agree to fp32 rounding (scores of magnitude 30: 1e-4), and are NaN
+    in the same places."""
+    B, K, S, A, H = (EXTREME_SIZES[k] for k in "BKSAH")
+    p = synth.with_sizes(synth.PRESETS["nematus_bf16_ln"], E=32, H=H, A=A, V=64, B=B, K=K, gemm=gemm, layer_norm=False)
+    w = synth.make_weights(p)
+    rng = np.random.default_rng(5)
+    if where == "queries":
+        w["Wa"] = synth.round_bf16((w["Wa"] * 60.0).astype(np.float32))
+    if where == "keys":
+        w["ba"] = (20.0 * rng.standard_normal(A)).astype(np.float32)
+    if where == "feature":
+        w["Wa"][:, 700] = 0.0
+        w["Wa"][3, 700] = 3e38
+    ctx = synth.round_bf16(np.tanh(rng.standard_normal((B, S, 2 * H))).astype(np.float32))
+    mask = (rng.random((B, S)) < 0.8).astype(np.float32)
+    mask[:, 7] = 1.0
+    if where == "position":
+        ctx[2, 7] *= 256.0
+    tok, src, state, _ = synth.mid_decode_inputs(p)
+    state = state[src].copy()
+    if where == "hypothesis":
+        w["Wa"] = synth.round_bf16((w["Wa"] * 8.0).astype(np.float32))
+        state *= np.float32(0.02)
+        state[K + 2] = np.sign(state[K + 2])
+    if where == "nan":
+        state[K + 2] = np.nan
+    rows = np.arange(p.M, dtype=np.int32)
+    out = []
+    for k in (K, 1):
+        dec = Decoder.from_preset(synth.with_sizes(p, B=p.M // k, K=k), w)
+        dec.set_batch(np.repeat(ctx, K // k, axis=0), np.repeat(mask, K // k, axis=0), k)
+        dec.precompute()
+        if out:
+            dec.pctx.copy_(out[0][1].repeat_interleave(K, 0))
+        q = run_step(dec, synth.with_sizes(p, B=p.M // k, K=k), tok, rows, T(state), p.M)
+        torch.cuda.synchronize()
+        out.append(({n: q[n].float().cpu().numpy() for n in ("alpha", "c", "s1")}, dec.pctx.clone()))
+    beam, row = out[0][0], out[1][0]
+    assert np.array_equal(beam["s1"], row["s1"], equal_nan=True)
+    for n in ("alpha", "c"):
+        assert np.array_equal(np.isnan(beam[n]), np.isnan(row[n])), n
+        assert np.isnan(beam[n]).any() == (where == "nan")
+        ok = ~np.isnan(row[n])
+        assert maxerr(beam[n][ok], row[n][ok]) <= (1e-4 if n == "alpha" or where != "position" else 256e-4), n
+
+
 def test_attention_row_form_still_serves():
     """Sizes the beam form leaves to the row form: A < 512, and weights beyond its LDS."""
     check("f32", 3, 4, 12, 496, 64)

@@ -52,6 +52,31 @@ def test_encoder_masks_with_holes(B, H, T, ln, gemm):
     assert err <= TOL[gemm]["state"]
 
 
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("B,S,H,T,ln", [(256, 5, 64, 0, False), (257, 5, 64, 0, False), (300, 5, 1024, 0, False),
+                                        (1030, 3, 64, 0, False), (200, 4, 1024, 1, False), (200, 4, 1024, 2, True)])
+def test_encoder_of_many_sentences(B, S, H, T, ln, gemm):
+    """Both sides of the one-launch form's 256 sentences; lists of more than 1024 sentences at a
+    position; recurrent products of both directions in one launch of the tiled kernel, over rows
+    counted on the device.  A sample of the sentences is compared at every position."""
+    src_V = 60
+    p, ew, dec = encoder(gemm, 48, H, src_V, T, ln)
+    rng = np.random.default_rng(B + H)
+    mask = (rng.random((B, S)) < 0.6).astype(np.float32)
+    mask[:, 0] = 1.0
+    mask[B - 2] = 0.0
+    src = rng.integers(0, src_V, size=(B, S)).astype(np.int32)
+    dec.set_source(src, mask, 1)
+    got = dec.ctx.float().cpu().numpy()
+    assert mt.mt_device_errors(dec.model) == 0
+    pick = [0, 1, 31, 32, B // 2, B - 3, B - 2, B - 1]
+    trans = tuple(ew[k] for k in synth.ENCODER_TRANSITION_NAMES) if T else None
+    lnp = tuple(ew[k] for k in synth.ENCODER_LN_NAMES if k in ew) if ln else None
+    ref = mtref.encode(src[pick], mask[pick], *[ew[k] for k in synth.ENCODER_NAMES], transitions=trans, ln=lnp, eps=1e-5)
+    assert maxerr(got[pick], ref) <= TOL[gemm]["state"]
+    assert np.isfinite(got).all() and np.abs(got).max() <= 1.0
+
+
 def test_encoder_flags_padded_tokens_out_of_range():
     p, ew, dec = encoder("f32", 48, 64, 50, 0, False)
     mask = np.array([[1, 1, 0]], np.float32)

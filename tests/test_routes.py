@@ -1,8 +1,10 @@
 """The rules that choose a kernel's form by the sizes of a call (host code, no GPU)."""
 import pytest
 
-from routes import attention_form, joint_chunks, vocab_chunks
-from test_gpu_attention_beam import BEAM
+import ctypes as C
+
+from routes import _fn, attention_form, joint_chunks, vocab_chunks
+from test_gpu_attention_beam import BEAM, EXTREME_SIZES
 from test_gpu_joint_pairs import PAIRS
 
 NEMATUS = dict(E=512, H=1024, A=2048)
@@ -11,6 +13,11 @@ NEMATUS = dict(E=512, H=1024, A=2048)
 @pytest.mark.parametrize("B,K,S,A,H", BEAM)
 def test_attention_beam_cases_take_the_beam_form(B, K, S, A, H):
     assert attention_form(B, K, S, 32, H, A) == "beam"
+
+
+def test_attention_beam_extremes_take_both_forms():
+    B, K, S, A, H = (EXTREME_SIZES[k] for k in "BKSAH")
+    assert attention_form(B, K, S, 32, H, A) == "beam" and attention_form(B * K, 1, S, 32, H, A) == "row"
 
 
 @pytest.mark.parametrize("B,K,S,dims,form", [
@@ -72,3 +79,13 @@ def test_joint_chunks_fit_the_single_models_workspace():
 ])
 def test_vocab_chunks(bf16, E, V, M, chunks):
     assert vocab_chunks(E, V, M, bf16) == chunks
+
+
+def test_weights_beyond_a_buffer_views_reach():
+    """Output weights of 4 GiB or more: no joint pass (and no unrolled k-loop) reads them through 32-bit
+    offsets."""
+    fits = _fn("_ZN2mt15vocab_fits_viewEiii", C.c_bool, 3)
+    rows = _fn("_ZN2mt16vocab_joint_rowsEiiii", C.c_int, 4)
+    for bf16, V in ((0, 1 << 21), (1, 1 << 22)):  # x 512 x 4 or 2 bytes
+        assert fits(bf16, V - 64, 512) and not fits(bf16, V, 512)
+        assert rows(bf16, V - 64, 512, 2) > 0 and rows(bf16, V, 512, 2) == 0
