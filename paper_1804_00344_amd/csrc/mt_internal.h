@@ -568,7 +568,8 @@ __device__ __forceinline__ void row_recompute_ens(const VocabView *vvs, const fl
 // launchers (host side).  All return hipSuccess or the launch error.
 // ---------------------------------------------------------------------------------------
 
-// EPI_SCATTER: row m is stored at output row o_idx[m], or a_idx[m] (the rows it was gathered from)
+// EPI_SCATTER: row m is stored at output row o_idx[m], or a_idx[m] (the rows it was gathered from);
+// the output rows increase with m (a tile whose last lies rows - 1 after its first is stored as a run)
 enum Epilogue { EPI_STORE = 0, EPI_TANH = 1, EPI_SCATTER = 2 };
 
 struct GemmProblem {

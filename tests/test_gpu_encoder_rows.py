@@ -77,6 +77,30 @@ def test_encoder_of_many_sentences(B, S, H, T, ln, gemm):
     assert np.isfinite(got).all() and np.abs(got).max() <= 1.0
 
 
+# the same through products and cells: tiles of consecutive rows beside
+# tiles with holes, in both tile kernels and with the last tile partly filled
+@pytest.mark.parametrize("gemm", ["f32", "bf16"])
+@pytest.mark.parametrize("B,S,H,T,holes", [(1030, 3, 1024, 0, 0.4), (330, 4, 1024, 0, 0.0), (330, 4, 1024, 0, 0.01),
+                                           (200, 4, 1024, 1, 0.0), (200, 4, 1024, 1, 0.01), (97, 4, 2048, 0, 0.02),
+                                           (160, 4, 768, 1, 0.02)])
+def test_encoder_products_store_runs_and_holes(B, S, H, T, holes, gemm):
+    src_V = 60
+    p, ew, dec = encoder(gemm, 48, H, src_V, T, False)
+    rng = np.random.default_rng(B + H)
+    mask = (rng.random((B, S)) >= holes).astype(np.float32)
+    mask[:, S - 1] = 1.0
+    src = rng.integers(0, src_V, size=(B, S)).astype(np.int32)
+    dec.set_source(src, mask, 1)
+    got = dec.ctx.float().cpu().numpy()
+    assert mt.mt_device_errors(dec.model) == 0
+    short = [int(b) for b in np.flatnonzero(mask.min(1) == 0)[:6]]
+    pick = sorted({0, 31, 32, 63, 64, 95, 96, B - 1, *short, *(min(b + 1, B - 1) for b in short)})
+    trans = tuple(ew[k] for k in synth.ENCODER_TRANSITION_NAMES) if T else None
+    ref = mtref.encode(src[pick], mask[pick], *[ew[k] for k in synth.ENCODER_NAMES], transitions=trans, ln=None, eps=1e-5)
+    assert maxerr(got[pick], ref) <= TOL[gemm]["state"]
+    assert np.isfinite(got).all() and np.abs(got).max() <= 1.0
+
+
 def test_encoder_flags_padded_tokens_out_of_range():
     p, ew, dec = encoder("f32", 48, 64, 50, 0, False)
     mask = np.array([[1, 1, 0]], np.float32)
