@@ -174,8 +174,8 @@ size_t mt_encode_workspace_bytes(const mt_model *model, int B, int S);
  *   mask [B,S] fp32 as for mt_precompute_ctx.  bf16 models keep the states in fp32 in the
  *   workspace and write their bf16 rounding (also the recurrent products' operand).
  * 1 <= S <= 1024; B*S <= 2^24.  One product for the input side of the valid positions; then a
- * shallow cell without layer norm takes one launch per position (up to 256 sentences), other
- * cells a recurrent product and a cell launch per block and position. */
+ * shallow cell without layer norm takes one launch per position (of a batch that the chip takes at
+ * once), other cells a recurrent product and a cell launch per block and position. */
 mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const float *mask, void *ctx_out,
                     void *ws, size_t ws_bytes, void *stream);
 

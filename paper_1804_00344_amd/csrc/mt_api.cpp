@@ -41,7 +41,6 @@ constexpr int kKPadFrag = 128;            // K padding of bf16 weights (one LDS 
 // (64 sentences x beam 12, their 5000 or so source positions, the sentences): a model serves
 // any batch, only the speed of other row counts may differ.
 constexpr long kRefRows = 768, kRefCtxRows = 4096, kRefSentences = 64;
-constexpr int kEncFusedSentences = 256;  // see mt_encode
 constexpr int kMaxTransitions = 16;  // recurrent-only GRU blocks after GRU 2
 
 size_t rup(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -731,10 +730,7 @@ mt_status mt_encode(mt_model *model, int B, int S, const int32_t *src_tok, const
   bf16 *tx16 = (bf16 *)(W + L.tx16);  // bf16 models: the operand of the next block's product
   float *const *eln = model->cfg.enc_layer_norm ? model->ln_enc : nullptr;
   const float eps = model->cfg.ln_eps;
-  // A shallow cell up to 256 sentences: one kernel per position.  Above, its 32-row groups read
-  // the weights too often (40 positions, two launches against one: bf16 128 sentences 675 / 487 us,
-  // 256 956 / 880, 1000 2645 / 3144; fp32 1586 / 1285, 2632 / 2499, 8930 / 9654).
-  if (Te == 0 && !eln && B <= kEncFusedSentences) {
+  if (Te == 0 && !eln && enc_step_takes(bf, B, H)) {
     if (bf) LAUNCH(MT_KERNEL_ENCODE, launch_fill_zero(sst, (long long)2 * B * H, st));
     EncStep e{};
     e.B = B; e.S = S; e.H = H;

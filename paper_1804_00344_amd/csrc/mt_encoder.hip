@@ -266,6 +266,26 @@ __global__ __launch_bounds__(kEncThreads) void enc_step_kernel(EncStep P) {
   if (BF) P.sst[((size_t)dir * B + b) * H + un] = v;
 }
 
+static constexpr int enc_row_blocks(int B) { return B <= 32 ? 1 : 2; }
+
+// Up to four workgroups per unit, and fewer of a wide cell, whose row groups each read all of its
+// weights (in fp32 at half the states' rate, so the line there lies earlier, and row groups of 32
+// that are not full cost most).  us for 24 positions, a product and a cell launch per position
+// against one kernel, sentences of full length / of mixed lengths:
+//   bf16 H = 256: 512 sentences 277 218 / 252 203, 1024 422 390 / 377 329;  512: 512 426 404 / 364 336,
+//   768 564 607 / 496 474;  1024: 160 370 355 / 327 294, 256 476 481 / 411 394, 300 487 552 / 418 431;
+//   1536: 160 517 524 / 445 429, 192 624 662 / 483 529;  2048: 96 532 532 / 486 453, 128 594 660 / 515 581
+//   fp32 H = 256: 1024 607 598 / 565 484;  512: 384 617 618 / 544 506, 768 985 1201 / 854 936;  768: 160 700
+//   571 / 702 541, 192 732 762 / 670 615, 256 871 833 / 747 676, 300 901 1035 / 788 800;  1024: 128 794 678 /
+//   728 594, 160 853 934 / 765 732, 256 1247 1281 / 1115 1035;  1536: 32 613 529 / 574 516, 33 712 798 / 696
+//   736, 128 1355 1322 / 1189 1181;  2048: 16 614 472 / 571 475, 48 965 1145 / 868 1025
+bool enc_step_takes(int bf16_mma, int B, int H) {
+  const int rb = enc_row_blocks(B);
+  const long wg = (long)((B + 16 * rb - 1) / (16 * rb)) * (H / kEncUnits) * 2;
+  if (bf16_mma) return wg <= 1024 && wg * H <= 1600 * 1024;
+  return wg <= 1024 && wg * H <= 600 * 1024 && (H <= 1024 || rb == 1);
+}
+
 template <typename CT, int PK, int RB>
 static hipError_t go_step_rb(const EncStep &p, hipStream_t st) {
   const dim3 grid((unsigned)((p.B + 16 * RB - 1) / (16 * RB) * (p.H / kEncUnits) * 2));
@@ -282,7 +302,7 @@ static hipError_t go_step_rb(const EncStep &p, hipStream_t st) {
 // 465).
 template <typename CT, int PK>
 static hipError_t go_step(const EncStep &p, hipStream_t st) {
-  return p.B <= 32 ? go_step_rb<CT, PK, 1>(p, st) : go_step_rb<CT, PK, 2>(p, st);
+  return enc_row_blocks(p.B) == 1 ? go_step_rb<CT, PK, 1>(p, st) : go_step_rb<CT, PK, 2>(p, st);
 }
 
 hipError_t launch_enc_step(int bf16_mma, const EncStep &p, hipStream_t st) {

@@ -723,6 +723,8 @@ struct EncStep {
   const int *acnt;
 };
 hipError_t launch_enc_step(int bf16_mma, const EncStep &p, hipStream_t st);
+// whether a batch of B sentences takes it (else a product and a cell launch per position)
+bool enc_step_takes(int bf16_mma, int B, int H);
 hipError_t launch_fill_zero(float *p, long long n, hipStream_t st);
 
 hipError_t launch_readout(int M, int E, const float *p1, int ld1, const float *p2, int ld2, const int32_t *idx2,

@@ -25,5 +25,10 @@ def joint_chunks(E, V, M, n=2, bf16=1, num_cu=256):
     return f(bf16, M, V, E, n, num_cu, C.byref(group)), group.value
 
 
+def encoder_form(B, H, bf16):
+    """"fused" (one kernel per position) or "products": a shallow encoder cell without layer norm."""
+    return "fused" if _fn("_ZN2mt14enc_step_takesEiii", C.c_bool, 3)(bf16, B, H) else "products"
+
+
 def vocab_chunks(E, V, M, bf16=1, num_cu=256):
     return _fn("_ZN2mt12vocab_chunksEiiiii", C.c_int, 5)(bf16, M, V, E, num_cu)

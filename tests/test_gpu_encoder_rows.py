@@ -77,13 +77,15 @@ def test_encoder_of_many_sentences(B, S, H, T, ln, gemm):
     assert np.isfinite(got).all() and np.abs(got).max() <= 1.0
 
 
-# the same through products and cells: tiles of consecutive rows beside
+# the same through products and cells (tests/test_routes.py has the rule): tiles of consecutive rows beside
 # tiles with holes, in both tile kernels and with the last tile partly filled
 @pytest.mark.parametrize("gemm", ["f32", "bf16"])
 @pytest.mark.parametrize("B,S,H,T,holes", [(1030, 3, 1024, 0, 0.4), (330, 4, 1024, 0, 0.0), (330, 4, 1024, 0, 0.01),
                                            (200, 4, 1024, 1, 0.0), (200, 4, 1024, 1, 0.01), (97, 4, 2048, 0, 0.02),
                                            (160, 4, 768, 1, 0.02)])
 def test_encoder_products_store_runs_and_holes(B, S, H, T, holes, gemm):
+    from routes import encoder_form
+    assert T or encoder_form(B, H, gemm == "bf16") == "products"
     src_V = 60
     p, ew, dec = encoder(gemm, 48, H, src_V, T, False)
     rng = np.random.default_rng(B + H)

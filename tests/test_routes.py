@@ -3,7 +3,7 @@ import pytest
 
 import ctypes as C
 
-from routes import _fn, attention_form, joint_chunks, vocab_chunks
+from routes import _fn, attention_form, encoder_form, joint_chunks, vocab_chunks
 from test_gpu_attention_beam import BEAM, EXTREME_SIZES
 from test_gpu_joint_pairs import PAIRS
 
@@ -89,3 +89,12 @@ def test_weights_beyond_a_buffer_views_reach():
     for bf16, V in ((0, 1 << 21), (1, 1 << 22)):  # x 512 x 4 or 2 bytes
         assert fits(bf16, V - 64, 512) and not fits(bf16, V, 512)
         assert rows(bf16, V - 64, 512, 2) > 0 and rows(bf16, V, 512, 2) == 0
+
+
+@pytest.mark.parametrize("bf16,H,most", [
+    # sentences up to which one kernel per position is the faster form, full lengths included
+    (1, 64, 4096), (1, 256, 1024), (1, 512, 512), (1, 1024, 256), (1, 1536, 160), (1, 2048, 96),
+    (0, 64, 4096), (0, 256, 1024), (0, 512, 512), (0, 768, 256), (0, 1024, 128), (0, 1536, 32), (0, 2048, 16),
+])
+def test_encoder_form(bf16, H, most):
+    assert [B for B in range(1, 5000) if encoder_form(B, H, bf16) == "fused"] == list(range(1, most + 1))
