@@ -364,19 +364,30 @@ static hipError_t go_wd_mb(const Problems &ps, int nprob, hipStream_t st) {
 }
 
 // Rows per tile, 32 MB: the fewest rounds of 256 workgroups (one per compute unit), weighted with
-// what a round of such tiles costs.  us for MB = 1, 2, 3, 4 (bf16 rows unless noted): 768 x 5120 x
-// 1024 18.6 15.6 19.5 17.6; 640 x 5120 x 1024 18.1 14.9 19.2 16.8; 768 x 3584 x 2048 24.8 22.4 21.0
-// 24.5; 1024 x 3584 x 2048 32.5 25.0 30.8 25.7; 768 x 3072 x 1024 (fp32 rows) 17.2 17.5 15.8 18.6;
-// 1024 x 3072 x 1024 (fp32 rows) 20.7 18.2 28.6 19.9; 320 x 3072 x 1024 8.4 10.4 13.8 16.8; 512 x
-// 3072 x 1024 12.2 11.2 14.5 17.5.  A unit's L1 delivers the 256 KB of weights and 64 MB KB of
-// activations of a tile (1024 k) at about 47 of its 64 bytes a clock, which is what a round costs.
+// what a round of such tiles costs against one of MB = 1.  us for MB = 1, 2, 3 (a graph of 20
+// launches): bf16 rows 768 x 5120 x 1024 18.7 15.8 18.9, 1024 x 5120 x 1024 23.8 20.8 20.2, 768 x 3584 x 2048
+// 24.9 21.8 19.9, 768 x 3072 x 1024 13.7 13.1 12.4, 2048 x 10240 x 2048 162 125 110.  fp32 rows, twice
+// the bytes and four conversions a vector, do better in the smaller tiles: 1536 x 3072 x 1024 31.2 27.4
+// 30.5, 896 x 5120 x 1024 27.1 24.1 28.2, 768 x 6144 x 512 17.0 16.5 19.0.  Deep products of many fp32 rows
+// read those from beyond the L2, once per tile column; tiles of 128 rows halve the weights' share
+// (MB = 2 / 4: 2048 x 2048 x 2048 44.7 / 33.1, 2048 x 6144 x 2048 125 / 94, 1792 x 3584 x 2048 69.6 / 59.8, 3072 x
+// 3584 x 2048 116 / 105; but 1024 x 3584 x 2048 30.4 / 30.7, 512 x 6144 x 2048 26.7 / 30.1, and 2048 x 1024 x 2048,
+// whose 128 tiles leave half of the units idle, 26.9 / 31.1).
+//
+// At 768 rows 1024 k cost 5.9 us of 3072 columns and 8.7 of 5120 (32 and 37 bytes of operands a
+// clock and unit); 6.5 and 7.5 us of a launch do not depend on the depth (row indices, first stage,
+// exchange, stores, the last tiles).
 template <typename AT, int EPI>
 static hipError_t go_wd(const Problems &ps, int nprob, hipStream_t st) {
-  static const double cost[3] = {5.2, 7.0, 10.5};  // of one round, launch excluded
+  constexpr bool F32 = sizeof(AT) == 4;
+  static const double cost[3] = {1.0, F32 ? 1.05 : 1.25, F32 ? 1.8 : 1.6};
   for (int i = 0; i < nprob; ++i) {
     const GemmProblem &p = ps.p[i];
     if (p.ldb % kWdStageK != 0 || p.K > p.ldb || p.K % 8 != 0) return hipErrorInvalidValue;
   }
+  if constexpr (F32)
+    if (ps.p[0].K >= 2048 && ps.p[0].M >= 1792 && (long)((ps.p[0].M + 127) / 128) * ((ps.p[0].N + 127) / 128) >= 224)
+      return go_wd_mb<AT, EPI, 4>(ps, nprob, st);
   int best = 1;
   double bc = 0;
   for (int mb = 1; mb <= 3; ++mb) {

@@ -38,3 +38,21 @@ def test_step_parity_few_rows(dims, B, K, gemm):
     for b in sents:  # the start state's product (tanh epilogue)
         err = float(np.max(np.abs(dec.s0[b].cpu().numpy() - orc[b]["s0"])))
         assert err <= TOL[gemm]["state"], (b, err)
+
+
+# Start states of many sentences in bf16, S = 1: fp32 rows (the context itself) against the tiles of 32,
+# 64, 96 and 128 rows (the last for depths from 2048 on), whole and partly filled last tiles
+@pytest.mark.parametrize("B,H", [(1504, 512), (2048, 512), (3001, 512), (4100, 512), (6144, 512), (5000, 512),
+                                 (1791, 2048), (1792, 2048), (1793, 2048), (2050, 1024), (3700, 1024)])
+def test_start_state_of_many_sentences(B, H):
+    p = synth.with_sizes(synth.PRESETS["tiny_bf16_ln"], E=16, H=H, A=16, V=50)
+    w = synth.make_weights(p)
+    dec = Decoder.from_preset(p, w)
+    rng = np.random.default_rng(B)
+    ctx = synth.round_bf16(np.tanh(rng.standard_normal((B, 1, 2 * H))).astype(np.float32))
+    dec.set_batch(ctx, np.ones((B, 1), np.float32), 1)
+    dec.precompute()
+    Wi, bi = (torch.from_numpy(w[k]).double().cuda() for k in ("Wi", "bi"))
+    ref = torch.tanh(torch.from_numpy(ctx[:, 0]).double().cuda() @ Wi + bi)
+    # both operands are bf16 values, the sums fp32
+    assert float((dec.s0.double() - ref).abs().max()) <= TOL["f32"]["state"]
