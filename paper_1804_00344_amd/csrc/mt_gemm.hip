@@ -803,7 +803,11 @@ static hipError_t go_f32(const Problems &ps, int nprob, hipStream_t st) {
 //    / 7.9, at 128 (896) 39.6 / 29.1, at 256 40.0 / 45.9;
 //  * fp32 in the 16-column packing, 256 up to 32 rows, else 512: recurrent at 32 rows (192) 7.1 / 6.7,
 //    at 64 (384) 10.6 / 9.8, sample at 128 (512) 8.0 / 6.0, but s1 at 5 rows (320) 6.7 / 8.1 and at 40
-//    (640) 10.8 / 13.1, two recurrent products at 5 (384) 7.2 / 8.2.
+//    (640) 10.8 / 13.1, two recurrent products at 5 (384) 7.2 / 8.2.  More than 256 workgroups are two
+//    rounds of the units, which only pays where the tiles are poor: at K = 64 768 x 256 (384) 3.9 /
+//    4.3 and at K = 256 two of 65 x 768 (288) 4.1 / 5.0 the tiles stay, at K = 128 they cannot split the
+//    depth (320 x 512 6.7 / 4.7), from K = 512 to 2048 256 x 1024 x 1024 (512) 10.7 / 9.6, at 4096 128 x 2048
+//    (512) 27.3 / 29.4.
 static bool small_rows(int bf16_mma, const Problems &ps, int nprob) {
   long wg = 0;
   for (int i = 0; i < nprob; ++i) {
@@ -811,7 +815,10 @@ static bool small_rows(int bf16_mma, const Problems &ps, int nprob) {
     if (p.K % 16 != 0 || p.M < 1 || p.wblk != ps.p[0].wblk) return false;
     wg += (long)((p.M + 31) / 32) * ((p.N + (bf16_mma ? 31 : 15)) / (bf16_mma ? 32 : 16));
   }
-  return wg <= (bf16_mma ? 512 : ps.p[0].wblk == 32 ? 896 : ps.p[0].M > 32 ? 512 : 256);
+  const int M = ps.p[0].M, K = ps.p[0].K;
+  if (bf16_mma) return wg <= 512;
+  if (ps.p[0].wblk == 32) return wg <= 896;
+  return wg <= (M > 32 && K >= 128 && K != 256 && K <= 2048 ? 512 : 256);
 }
 
 hipError_t launch_gemm(int bf16_mma, const GemmProblem *probs, int nprob, Epilogue epi, hipStream_t st) {
