@@ -91,7 +91,8 @@ __device__ __forceinline__ OutRows out_rows_of(int first, int last, int rows) {
 // pass through LDS in stages of 128 k (bf16, an fp32 operand rounded
 // on the way), double-buffered from two register stages with one barrier per 8 k-steps; each
 // wave's weight fragments come through a register ring refilled D k-steps ahead, so the only
-// LDS traffic is the activations (written once, read by both waves).
+// LDS traffic is the activations (written once; a row's fragment is read by the two waves, one of
+// each column half, that own its k-step).
 //
 // The KW = 2 waves of a column half share its k-steps (of the 8 of a stage, wave kh takes 4), and
 // at the end exchange halves of their partial tiles through LDS, each finishing one 32-column
@@ -223,8 +224,8 @@ __global__ __launch_bounds__(kWdThreads) void gemm_wd_kernel(Problems probs) {
 
   // The wave's k-steps of stage st from LDS buffer buf; the ring slots of stage st are
   // (SPS * (st & 1) + s) % D, static in the two-stage unrolled loop below.  The activation
-  // fragments of k-step s + 1 are read before the MFMAs of k-step s (one wave per SIMD: nothing
-  // else would cover the LDS latency).
+  // fragments of k-step s + 1 are read before the MFMAs of k-step s (a SIMD holds one or two waves,
+  // which meet at the stages' barriers: little else covers the LDS latency).
   const int arow = lane & 31, akoff = (lane >> 5) * 16;
   auto compute = [&](int st, int buf, auto par) {
     const char *base = lds + buf * kWdStage + arow * kWdRowBytes + akoff + kh * (SPS * 32);

@@ -6,11 +6,12 @@
 // latency of a workgroup's chain of loads.  Tiles of 64 x 128 outputs leave 24 to 40 workgroups
 // whose two waves walk the whole depth alone.  Here one workgroup of eight waves owns one
 // column block of the packed weights (16 or 32 columns) and 32 rows, and the waves split the
-// k-steps: each issues the loads of eight k-steps at once (both operands straight from global
-// memory into registers, no barrier), then the eight partial tiles are added through LDS in
-// wave order.  Row groups of 32 share a column block's weights in one XCD's L2.  5 rows of the
-// bf16 step: 3072 x 1024 8.2 -> 4.4 us, 5120 x 1024 7.8 -> 4.5, 3584 x 2048 11.7 -> 5.5, 512 x 1024
-// 7.4 -> 3.6; fp32 3584 x 2048 38.5 -> 7.9 us at 5 rows, 39.5 -> 17.4 at 64.
+// k-steps in chunks of 64 k (four k-steps): the weights of a chunk go straight into registers, the
+// activations through the wave's own part of LDS (no workgroup barrier), both requested one chunk
+// ahead; then the eight partial tiles are added through LDS in wave order.  Row groups of 32 share
+// a column block's weights in one XCD's L2.  5 rows of the bf16 step: 3072 x 1024 8.2 -> 4.4 us,
+// 5120 x 1024 7.8 -> 4.5, 3584 x 2048 11.7 -> 5.5, 512 x 1024 7.4 -> 3.6; fp32 3584 x 2048 38.5 -> 7.9 us
+// at 5 rows, 39.5 -> 17.4 at 64.  enc_step_kernel (mt_encoder.hip) splits the depth in the same way.
 #include "mt_gemm_common.h"
 
 namespace mt {
