@@ -303,13 +303,13 @@ def main():
                   "TOPK": "topk_row_select", "VOCAB_THRESHOLD": "vocab_threshold", "LSE": "lse"}
         for k, cls in cls_of.items():
             ent = breakdown.get(k.lower())
-            hits = [e for key, e in tf.items() if key.startswith(cls + "@")]
+            hits = [e for key, e in tf.items() if key.startswith(cls + "@")][:1]
+            if cls == "attention" and not hits:  # the beam form: two kernels
+                hits = [e for key, e in tf.items() if key.startswith(("attention_scores@", "attention_context@"))]
             if not ent or not hits:
                 continue
-            e = hits[0]
-            src = os.path.join(ROOT, "paper_1804_00344_amd", "csrc", e["source"])
-            if os.path.exists(src) and source_hash(src) == e["source_hash"]:
-                ent["counter_MB_per_launch"] = round(e["bytes_per_launch"] / 1e6, 3)
+            if all(source_hash(os.path.join(ROOT, "paper_1804_00344_amd", "csrc", e["source"])) == e["source_hash"] for e in hits):
+                ent["counter_MB_per_launch"] = round(sum(e["bytes_per_launch"] for e in hits) / 1e6, 3)
 
     # the materialised selection: mt_beam_topk reading a [M, V] fp32 log-probability matrix
     # (ensembles, or callers that want the log-probabilities), an HBM-bound first level

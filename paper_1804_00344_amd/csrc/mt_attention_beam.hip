@@ -370,6 +370,7 @@ static hipError_t beam_go(int B, int K, int S, int A, int Cd, const T *P, const 
   // with 6 23.1 16.8 15.5 15.4, with 4 24.0 17.7 16.6 18.4; 128 x 5 (mean 30, longest 100) with 5
   // 22.6 16.6 16.3 18.1; 8 x 5 (mean 25, longest 60) with 5 4.7 4.5 5.6 7.9: more of either shares
   // the exponentials further, fewer leave more waves to cover the latency and even out the units.
+  // One position up to 1280 padded ones (the valid ones are not known on the host), four from 5120.
   const long pt = (long)B * S / 1280;
   const int PT = pt < 1 ? 1 : pt > kScoreSlots ? kScoreSlots : (int)pt;
   const int ng = (K + 5) / 6, kn = (K + ng - 1) / ng;

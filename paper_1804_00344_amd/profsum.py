@@ -113,13 +113,19 @@ KERNEL_CLASSES = [
     ("vocab_kernel", "vocab_gemm", "mt_vocab.hip"),
     ("attention_order_kernel", "attention_order", "mt_attention.hip"),
     ("attention_kernel", "attention", "mt_attention.hip"),
+    ("attn_score_kernel", "attention_scores", "mt_attention_beam.hip"),
+    ("attn_context_kernel", "attention_context", "mt_attention_beam.hip"),
     ("gru_cell_kernel", "gru_cell", "mt_rnn.hip"),
     ("readout_kernel", "readout", "mt_rnn.hip"),
     ("lse_kernel", "lse", "mt_rnn.hip"),
     ("row_select_kernel", "topk_row_select", "mt_topk.hip"),
+    ("sentence_select_kernel", "topk_sentence_select", "mt_topk.hip"),
     ("topk_scan_logp_kernel", "topk_scan_logp", "mt_topk.hip"),
     ("gemm_wd_kernel", "gemm_bf16", "mt_gemm.hip"),
     ("gemm_f32_kernel", "gemm_f32", "mt_gemm.hip"),
+    ("gemm_small_kernel", "gemm_few_rows", "mt_gemm_small.hip"),
+    ("enc_step_kernel", "encoder_position", "mt_encoder.hip"),
+    ("enc_lists_kernel", "encoder_lists", "mt_encoder.hip"),
 ]
 
 
